@@ -134,16 +134,32 @@ int check_mlp(const pinsage_mlp_t* M) {
   return PINSAGE_OK;
 }
 
-size_t mlp_ws(const pinsage_mlp_t* M, int64_t n) {
+// Products of at least this many rows take their fp32 weights split once
+// (split_b_bytes of workspace each) rather than in every tile: 1.2M x 256 ->
+// 256 takes 1.01 ms instead of 1.11. At 16K rows (about 25 us) the saving and the
+// split's own launch (about 5 us) are equal. A workspace without room for the split weights is accepted all the
+// same; the tiles then split them, to the same bits.
+constexpr int64_t kSplitRows = 1ll << 14;
+inline size_t split_ws(pinsage_dtype_t dtype, int64_t rows, int n, int k) {
+  return dtype == PINSAGE_F32 && rows >= kSplitRows ? align_up(split_b_bytes(n, k)) : 0;
+}
+
+// Hidden rows | split G1 | split G2 (the last two when `pre`).
+size_t mlp_ws(const pinsage_mlp_t* M, int64_t n, bool pre) {
   const int64_t chunk = n < kChunkRows ? n : kChunkRows;
-  return align_up((size_t)chunk * M->d_hidden * elem_size(M->dtype));
+  const size_t hidden = align_up((size_t)chunk * M->d_hidden * elem_size(M->dtype));
+  return hidden + (pre ? split_ws(M->dtype, n, M->d_hidden, M->d_in) +
+                             split_ws(M->dtype, n, M->d_out, M->d_hidden)
+                       : 0);
 }
 
 // z = G2 ReLU(G1 h + g) in row chunks (hidden activations in the workspace).
 int run_mlp(const pinsage_mlp_t* M, const void* h, const int32_t* rowmap, int64_t n_h,
-            int64_t n, void* z, void* ws, hipStream_t s) {
+            int64_t n, void* z, void* ws, bool pre, hipStream_t s) {
   const size_t es = elem_size(M->dtype);
   const bool bf16 = M->dtype == PINSAGE_BF16;
+  const size_t s1 = pre ? split_ws(M->dtype, n, M->d_hidden, M->d_in) : 0;
+  unsigned char* const split1 = static_cast<unsigned char*>(ws) + mlp_ws(M, n, false);
   for (int64_t r0 = 0; r0 < n; r0 += kChunkRows) {
     const int64_t rows = (n - r0) < kChunkRows ? (n - r0) : kChunkRows;
     GemmLaunch g1{};
@@ -165,6 +181,7 @@ int run_mlp(const pinsage_mlp_t* M, const void* h, const int32_t* rowmap, int64_
     g1.bf16 = bf16;
     g1.relu = true;
     g1.prof_class = kKMlp;
+    if (s1) g1.Bs = split1;
     hipError_t e = launch_gemm(g1, s);
     if (e != hipSuccess) return hip_fail(e, "output layer G1 launch");
     GemmLaunch g2{};
@@ -178,6 +195,7 @@ int run_mlp(const pinsage_mlp_t* M, const void* h, const int32_t* rowmap, int64_
     g2.C = static_cast<unsigned char*>(z) + (size_t)r0 * M->d_out * es;
     g2.bf16 = bf16;
     g2.prof_class = kKMlp;
+    if (s1) g2.Bs = split1 + s1;
     e = launch_gemm(g2, s);
     if (e != hipSuccess) return hip_fail(e, "output layer G2 launch");
   }
@@ -207,10 +225,14 @@ int check_nbr(const pinsage_neighborhoods_t* n, int64_t rows, const char* what) 
 //   DENSE_THEN_POOL, bf16, d_in = d_out = 256: + W_s as product fragments for
 //                    the fused pool and W kernel (used when top_t <= 64; the
 //                    pooled chunk then stays unused).
+//   fp32, when `pre`: + Q's, W_n's and W's (or W_s's) splits, Q's and W_n's
+//                    twice (one per stream of the overlapped schedule).
 struct LayerWs {
   size_t table = 0, pchunk = 0, pooled = 0, wsp = 0;
+  size_t qs = 0, wns = 0, wss = 0;
   bool chained = false;
-  size_t total() const { return table + pchunk + pooled + wsp; }
+  size_t base() const { return table + pchunk + pooled + wsp; }
+  size_t total() const { return base() + 2 * (qs + wns) + wss; }
 };
 
 bool chained_layer(const pinsage_layer_t* L) {
@@ -218,7 +240,7 @@ bool chained_layer(const pinsage_layer_t* L) {
          chain_supported(L->d_in, L->m, L->d_out, L->dtype == PINSAGE_BF16);
 }
 
-LayerWs layer_ws(const pinsage_layer_t* L, int64_t n_transform, int64_t n_out) {
+LayerWs layer_ws(const pinsage_layer_t* L, int64_t n_transform, int64_t n_out, bool pre) {
   const size_t es = elem_size(L->dtype);
   const int64_t out_chunk = n_out < kChunkRows ? n_out : kChunkRows;
   const int64_t tr_chunk = n_transform < kChunkRows ? n_transform : kChunkRows;
@@ -235,18 +257,24 @@ LayerWs layer_ws(const pinsage_layer_t* L, int64_t n_transform, int64_t n_out) {
     w.table = align_up((size_t)n_transform * L->m * es);
     w.pooled = align_up((size_t)out_chunk * L->m * es);
   }
+  if (pre) {
+    const bool split = L->dataflow == PINSAGE_DENSE_THEN_POOL;
+    w.qs = split_ws(L->dtype, n_transform, L->m, L->d_in);
+    if (split) w.wns = split_ws(L->dtype, n_transform, L->d_out, L->m);
+    w.wss = split_ws(L->dtype, n_out, L->d_out, split ? L->d_in : L->d_in + L->m);
+  }
   return w;
 }
 
-size_t convolve_ws(const pinsage_layer_t* L, int64_t n_transform, int64_t n_out) {
-  return layer_ws(L, n_transform, n_out).total();
+size_t convolve_ws(const pinsage_layer_t* L, int64_t n_transform, int64_t n_out, bool pre) {
+  return layer_ws(L, n_transform, n_out, pre).total();
 }
 
 // Algorithm 1 line 1 for rows [c0, c0 + rows) of the transformed set:
 // C = ReLU(h_in[t(i)] Q^T + q).
 hipError_t launch_transform(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
                             const int32_t* transform_rows, int64_t c0, int64_t rows, void* C,
-                            hipStream_t s) {
+                            void* Bs, hipStream_t s) {
   const size_t es = elem_size(L->dtype);
   GemmLaunch g{};
   if (transform_rows) {
@@ -267,6 +295,7 @@ hipError_t launch_transform(const pinsage_layer_t* L, const void* h_in, int64_t 
   g.bf16 = L->dtype == PINSAGE_BF16;
   g.relu = true;
   g.row_base = c0;
+  g.Bs = Bs;
   return launch_gemm(g, s);
 }
 
@@ -279,17 +308,22 @@ hipError_t launch_transform(const pinsage_layer_t* L, const void* h_in, int64_t 
 // row ranges with disjoint P rows can run on two streams at once.
 int run_transform_rows(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
                        int64_t n_transform, const int32_t* transform_rows, int64_t n_out,
-                       void* ws, int64_t r0, int64_t r1, int64_t pbase, hipStream_t s) {
+                       void* ws, bool pre, int64_t r0, int64_t r1, int64_t pbase,
+                       hipStream_t s) {
   const bool bf16 = L->dtype == PINSAGE_BF16;
   const size_t es = elem_size(L->dtype);
-  const LayerWs lw = layer_ws(L, n_transform, n_out);
+  const LayerWs lw = layer_ws(L, n_transform, n_out, pre);
   unsigned char* table = static_cast<unsigned char*>(ws);  // P, or R when split
+  // This stream's split Q and W_n.
+  unsigned char* const splits = table + lw.base() + (r0 > 0 ? lw.qs + lw.wns : 0);
+  void* const qs = lw.qs ? splits : nullptr;
+  void* const wns = lw.wns ? splits + lw.qs : nullptr;
   hipError_t e;
   if (r1 <= r0) return PINSAGE_OK;
   if (L->dataflow != PINSAGE_DENSE_THEN_POOL) {
     // Algorithm 1 line 1, once per transformable row (Sec. 3.4).
     e = launch_transform(L, h_in, n_in, transform_rows, r0, r1 - r0,
-                         table + (size_t)r0 * L->m * es, s);
+                         table + (size_t)r0 * L->m * es, qs, s);
     if (e != hipSuccess) return hip_fail(e, "Q transform launch");
     return PINSAGE_OK;
   }
@@ -324,7 +358,7 @@ int run_transform_rows(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
   const int64_t cs = kChunkRows - pbase;
   for (int64_t c0 = r0; c0 < r1; c0 += cs) {
     const int64_t rows = (r1 - c0) < cs ? (r1 - c0) : cs;
-    e = launch_transform(L, h_in, n_in, transform_rows, c0, rows, pchunk, s);
+    e = launch_transform(L, h_in, n_in, transform_rows, c0, rows, pchunk, qs, s);
     if (e != hipSuccess) return hip_fail(e, "Q transform launch");
     GemmLaunch gr{};
     gr.A0 = pchunk;
@@ -338,6 +372,7 @@ int run_transform_rows(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
     gr.C = table + (size_t)c0 * L->d_out * es;
     gr.bf16 = bf16;
     gr.row_base = c0;
+    gr.Bs = wns;
     e = launch_gemm(gr, s);
     if (e != hipSuccess) return hip_fail(e, "neighbour-half W launch");
   }
@@ -345,19 +380,20 @@ int run_transform_rows(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
 }
 
 int run_transform(const pinsage_layer_t* L, const void* h_in, int64_t n_in, int64_t n_transform,
-                  const int32_t* transform_rows, int64_t n_out, void* ws, hipStream_t s) {
-  return run_transform_rows(L, h_in, n_in, n_transform, transform_rows, n_out, ws, 0,
+                  const int32_t* transform_rows, int64_t n_out, void* ws, bool pre,
+                  hipStream_t s) {
+  return run_transform_rows(L, h_in, n_in, n_transform, transform_rows, n_out, ws, pre, 0,
                             n_transform, 0, s);
 }
 
 int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
                    int64_t n_transform, const pinsage_neighborhoods_t* nbr,
-                   const int32_t* self_rows, void* h_out, int64_t n_out, void* ws,
+                   const int32_t* self_rows, void* h_out, int64_t n_out, void* ws, bool pre,
                    hipStream_t s) {
   const bool bf16 = L->dtype == PINSAGE_BF16;
   const bool split = L->dataflow == PINSAGE_DENSE_THEN_POOL;
   const size_t es = elem_size(L->dtype);
-  const LayerWs lw = layer_ws(L, n_transform, n_out);
+  const LayerWs lw = layer_ws(L, n_transform, n_out, pre);
   unsigned char* table = static_cast<unsigned char*>(ws);
   unsigned char* nbuf = table + lw.table + lw.pchunk;
   const int pool_width = split ? L->d_out : L->m;
@@ -436,6 +472,7 @@ int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
     gw.relu = true;
     gw.l2norm = true;
     gw.row_base = r0;
+    if (lw.wss) gw.Bs = table + lw.base() + 2 * (lw.qs + lw.wns);
     e = launch_gemm(gw, s);
     if (e != hipSuccess) return hip_fail(e, "W transform launch");
   }
@@ -444,10 +481,11 @@ int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
 
 int run_layer(const pinsage_layer_t* L, const void* h_in, int64_t n_in, int64_t n_transform,
               const int32_t* transform_rows, const pinsage_neighborhoods_t* nbr,
-              const int32_t* self_rows, void* h_out, int64_t n_out, void* ws, hipStream_t s) {
-  int st = run_transform(L, h_in, n_in, n_transform, transform_rows, n_out, ws, s);
+              const int32_t* self_rows, void* h_out, int64_t n_out, void* ws, bool pre,
+              hipStream_t s) {
+  int st = run_transform(L, h_in, n_in, n_transform, transform_rows, n_out, ws, pre, s);
   if (st) return st;
-  return run_pool_dense(L, h_in, n_in, n_transform, nbr, self_rows, h_out, n_out, ws, s);
+  return run_pool_dense(L, h_in, n_in, n_transform, nbr, self_rows, h_out, n_out, ws, pre, s);
 }
 
 // ---- walks beside the first layer's transform (embed_all) -----------------
@@ -800,7 +838,7 @@ struct BipartiteWs {
   size_t total() const { return conv + (size_t)hbufs * h + map; }
 };
 int bipartite_ws(const pinsage_graph_t* graph, const pinsage_layer_t* layers, int32_t K,
-                 BipartiteWs* w) {
+                 bool pre, BipartiteWs* w) {
   int st;
   if (K < 1 || !layers) return fail(PINSAGE_EINVAL, "need at least one layer");
   if (K % 2)
@@ -814,7 +852,7 @@ int bipartite_ws(const pinsage_graph_t* graph, const pinsage_layer_t* layers, in
     if (k > 0 && layers[k].d_in != layers[k - 1].d_out)
       return fail(PINSAGE_EINVAL, "layer %d d_in %d != layer %d d_out %d", k, layers[k].d_in,
                   k - 1, layers[k - 1].d_out);
-    const size_t c = convolve_ws(&layers[k], n, n);
+    const size_t c = convolve_ws(&layers[k], n, n, pre);
     w->conv = c > w->conv ? c : w->conv;
     if (k + 1 < K) {
       const size_t hb = align_up((size_t)n * layers[k].d_out * elem_size(layers[k].dtype));
@@ -889,7 +927,7 @@ int pinsage_embed_all_bipartite_workspace_size(const pinsage_graph_t* graph,
   if (st) return st;
   if (!bytes) return fail(PINSAGE_EINVAL, "bytes is NULL");
   BipartiteWs w;
-  if ((st = bipartite_ws(graph, layers, num_layers, &w))) return st;
+  if ((st = bipartite_ws(graph, layers, num_layers, true, &w))) return st;
   *bytes = w.total();
   return PINSAGE_OK;
 }
@@ -903,7 +941,12 @@ int pinsage_embed_all_bipartite(const pinsage_graph_t* graph, uint64_t seed,
   int st = check_graph(graph);
   if (st) return st;
   BipartiteWs w;
-  if ((st = bipartite_ws(graph, layers, num_layers, &w))) return st;
+  if ((st = bipartite_ws(graph, layers, num_layers, true, &w))) return st;
+  const bool pre = workspace_bytes >= w.total();
+  if (!pre) {
+    w = BipartiteWs{};
+    if ((st = bipartite_ws(graph, layers, num_layers, false, &w))) return st;
+  }
   const int64_t n = graph->num_pins + graph->num_boards;
   if ((st = check_nbr(nbr_out, n, "embed_all_bipartite"))) return st;
   if (!x_pins || !h_out) return fail(PINSAGE_EINVAL, "x_pins or h_out is NULL");
@@ -926,9 +969,10 @@ int pinsage_embed_all_bipartite(const pinsage_graph_t* graph, uint64_t seed,
   for (int k = 0; k < num_layers; ++k) {
     void* dst = (k == num_layers - 1) ? h_out : hbuf[k % 2];
     if (k == 0)
-      st = run_layer(&layers[k], cur, graph->num_pins, n, pin_map, nbr_out, pin_map, dst, n, ws, s);
+      st = run_layer(&layers[k], cur, graph->num_pins, n, pin_map, nbr_out, pin_map, dst, n, ws,
+                     pre, s);
     else
-      st = run_layer(&layers[k], cur, n, n, nullptr, nbr_out, nullptr, dst, n, ws, s);
+      st = run_layer(&layers[k], cur, n, n, nullptr, nbr_out, nullptr, dst, n, ws, pre, s);
     if (st) return st;
     cur = dst;
   }
@@ -942,7 +986,7 @@ int pinsage_convolve_workspace_size(const pinsage_layer_t* layer, int64_t n_tran
   if (st) return st;
   if (!bytes) return fail(PINSAGE_EINVAL, "bytes is NULL");
   if (n_transform < 0 || n_out < 0) return fail(PINSAGE_EINVAL, "negative row count");
-  *bytes = convolve_ws(layer, n_transform, n_out);
+  *bytes = convolve_ws(layer, n_transform, n_out, true);
   return PINSAGE_OK;
 }
 
@@ -956,13 +1000,14 @@ int pinsage_convolve_layer(const pinsage_layer_t* layer, const void* h_in, int64
                           n_out);
   if (st) return st;
   if (n_out == 0 && n_transform == 0) return PINSAGE_OK;
-  const size_t need = convolve_ws(layer, n_transform, n_out);
+  const size_t need = convolve_ws(layer, n_transform, n_out, false);
   if (need > 0 && (!workspace || workspace_bytes < need))
     return fail(PINSAGE_EWORKSPACE, "workspace %zu bytes < required %zu", workspace_bytes, need);
   if (reinterpret_cast<uintptr_t>(workspace) % 256)
     return fail(PINSAGE_EINVAL, "workspace is not 256-byte aligned");
   return run_layer(layer, h_in, n_in, n_transform, transform_rows, nbr, self_rows, h_out, n_out,
-                   workspace, static_cast<hipStream_t>(stream));
+                   workspace, workspace_bytes >= convolve_ws(layer, n_transform, n_out, true),
+                   static_cast<hipStream_t>(stream));
 }
 
 int pinsage_convolve_layer_noalloc(const pinsage_layer_t* layer, const void* h_in, int64_t n_in,
@@ -974,7 +1019,7 @@ int pinsage_convolve_layer_noalloc(const pinsage_layer_t* layer, const void* h_i
                           n_out);
   if (st) return st;
   if (n_out == 0 && n_transform == 0) return PINSAGE_OK;
-  const size_t need = convolve_ws(layer, n_transform, n_out);
+  const size_t need = convolve_ws(layer, n_transform, n_out, false);
   if (need > kScratchBytes)
     return fail(PINSAGE_EUNSUPPORTED,
                 "layer needs %zu bytes of scratch (n_transform %lld, n_out %lld); the static "
@@ -985,7 +1030,34 @@ int pinsage_convolve_layer_noalloc(const pinsage_layer_t* layer, const void* h_i
   // Every scratch region the layer reads (P or R rows, the pooled chunk) is
   // written earlier in the same call, so nothing has to start at zero.
   return run_layer(layer, h_in, n_in, n_transform, transform_rows, nbr, self_rows, h_out, n_out,
-                   ws, static_cast<hipStream_t>(stream));
+                   ws, kScratchBytes >= convolve_ws(layer, n_transform, n_out, true),
+                   static_cast<hipStream_t>(stream));
+}
+
+// Workspace of the all-node job: the layers' region, then the h buffers. The
+// walk table shares the layers' region: the in-order walks finish before the
+// first transform writes it.
+struct EmbedWs {
+  size_t conv = 0, h = 0;
+  int hbufs = 0;
+  size_t total() const { return conv + (size_t)hbufs * h; }
+};
+static EmbedWs embed_ws(const pinsage_graph_t* graph, const pinsage_layer_t* layers,
+                        int32_t num_layers, bool pre) {
+  const int64_t n = graph->num_pins + graph->num_boards;
+  EmbedWs w;
+  for (int k = 0; k < num_layers; ++k) {
+    const size_t c = convolve_ws(&layers[k], graph->num_pins, n, pre);
+    w.conv = c > w.conv ? c : w.conv;
+    if (k + 1 < num_layers) {
+      const size_t hb = align_up((size_t)n * layers[k].d_out * elem_size(layers[k].dtype));
+      w.h = hb > w.h ? hb : w.h;
+    }
+  }
+  const size_t tb = walk_table_bytes(graph);
+  w.conv = tb > w.conv ? tb : w.conv;
+  w.hbufs = num_layers > 2 ? 2 : (num_layers > 1 ? 1 : 0);
+  return w;
 }
 
 int pinsage_embed_all_workspace_size(const pinsage_graph_t* graph, const pinsage_layer_t* layers,
@@ -995,22 +1067,9 @@ int pinsage_embed_all_workspace_size(const pinsage_graph_t* graph, const pinsage
   if (st) return st;
   if (!bytes) return fail(PINSAGE_EINVAL, "bytes is NULL");
   if (num_layers < 1 || !layers) return fail(PINSAGE_EINVAL, "need at least one layer");
-  const int64_t n = graph->num_pins + graph->num_boards;
-  size_t conv = 0, h = 0;
-  for (int k = 0; k < num_layers; ++k) {
+  for (int k = 0; k < num_layers; ++k)
     if ((st = check_layer(&layers[k], k))) return st;
-    const size_t c = convolve_ws(&layers[k], graph->num_pins, n);
-    conv = c > conv ? c : conv;
-    if (k + 1 < num_layers) {
-      const size_t hb = align_up((size_t)n * layers[k].d_out * elem_size(layers[k].dtype));
-      h = hb > h ? hb : h;
-    }
-  }
-  const int hbufs = num_layers > 2 ? 2 : (num_layers > 1 ? 1 : 0);
-  // The walk table shares the layers' region: the in-order walks finish before
-  // the first transform writes it.
-  const size_t tb = walk_table_bytes(graph);
-  *bytes = (conv > tb ? conv : tb) + (size_t)hbufs * h;
+  *bytes = embed_ws(graph, layers, num_layers, true).total();
   return PINSAGE_OK;
 }
 
@@ -1038,24 +1097,16 @@ int pinsage_embed_all(const pinsage_graph_t* graph, const pinsage_walk_params_t*
     return fail(PINSAGE_EINVAL, "nbr_out->top_t %d != walk->top_t %d", nbr_out->top_t,
                 walk->top_t);
   if (!x || !h_out) return fail(PINSAGE_EINVAL, "x or h_out is NULL");
-  size_t need = 0;
-  if ((st = pinsage_embed_all_workspace_size(graph, layers, num_layers, &need))) return st;
-  if (!workspace || workspace_bytes < need)
-    return fail(PINSAGE_EWORKSPACE, "workspace %zu bytes < required %zu", workspace_bytes, need);
+  EmbedWs w = embed_ws(graph, layers, num_layers, true);
+  const bool pre = workspace_bytes >= w.total();
+  if (!pre) w = embed_ws(graph, layers, num_layers, false);
+  if (!workspace || workspace_bytes < w.total())
+    return fail(PINSAGE_EWORKSPACE, "workspace %zu bytes < required %zu", workspace_bytes,
+                w.total());
   if (reinterpret_cast<uintptr_t>(workspace) % 256)
     return fail(PINSAGE_EINVAL, "workspace is not 256-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  size_t conv = 0, h = 0;
-  for (int k = 0; k < num_layers; ++k) {
-    const size_t c = convolve_ws(&layers[k], graph->num_pins, n);
-    conv = c > conv ? c : conv;
-    if (k + 1 < num_layers) {
-      const size_t hb = align_up((size_t)n * layers[k].d_out * elem_size(layers[k].dtype));
-      h = hb > h ? hb : h;
-    }
-  }
-  const size_t tb = walk_table_bytes(graph);
-  if (tb > conv) conv = tb;
+  const size_t conv = w.conv, h = w.h, tb = walk_table_bytes(graph);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   unsigned char* hbuf[2] = {ws + conv, ws + conv + h};
   const int64_t P = graph->num_pins;
@@ -1098,7 +1149,7 @@ int pinsage_embed_all(const pinsage_graph_t* graph, const pinsage_walk_params_t*
       // Every record and wait below runs whatever the launches returned, so
       // the side and walk streams are joined back into the caller's stream
       // on error paths too (no work of this call is left unjoined).
-      st = run_transform_rows(L0, x, n, P, nullptr, n, ws, 0, a, 0, ov.side);
+      st = run_transform_rows(L0, x, n, P, nullptr, n, ws, pre, 0, a, 0, ov.side);
       const hipError_t e1 = hipEventRecord(ov.side_done, ov.side);
       if (!st && ov_table) {
         const hipError_t et = launch_walk_table(graph->row_offsets,
@@ -1113,7 +1164,7 @@ int pinsage_embed_all(const pinsage_graph_t* graph, const pinsage_walk_params_t*
       // Join: the caller's stream waits for the walks before its share of
       // the transform, and for the side before the pool.
       const hipError_t e3 = hipStreamWaitEvent(s, ov.walk_done, 0);
-      if (!st) st = run_transform_rows(L0, x, n, P, nullptr, n, ws, a, P, a, s);
+      if (!st) st = run_transform_rows(L0, x, n, P, nullptr, n, ws, pre, a, P, a, s);
       const hipError_t e4 = hipEventRecord(ov.main_done, s);
       const hipError_t e5 = hipStreamWaitEvent(s, ov.side_done, 0);
       if (st) return st;
@@ -1136,14 +1187,14 @@ int pinsage_embed_all(const pinsage_graph_t* graph, const pinsage_walk_params_t*
     }
     const void* tab = gtab ? gtab : (tb ? ws : nullptr);
     if ((st = run_walks(graph, walk, nullptr, n, nbr_out, total_steps, tab, s))) return st;
-    if ((st = run_transform(L0, x, n, P, nullptr, n, ws, s))) return st;
+    if ((st = run_transform(L0, x, n, P, nullptr, n, ws, pre, s))) return st;
   }
 
   const void* cur = x;
   for (int k = 0; k < num_layers; ++k) {
     void* dst = (k == num_layers - 1) ? h_out : hbuf[k % 2];
-    if (k > 0) st = run_transform(&layers[k], cur, n, P, nullptr, n, ws, s);
-    if (!st) st = run_pool_dense(&layers[k], cur, n, P, nbr_out, nullptr, dst, n, ws, s);
+    if (k > 0) st = run_transform(&layers[k], cur, n, P, nullptr, n, ws, pre, s);
+    if (!st) st = run_pool_dense(&layers[k], cur, n, P, nbr_out, nullptr, dst, n, ws, pre, s);
     if (st) return st;
     cur = dst;
   }
@@ -1281,7 +1332,7 @@ int pinsage_output_mlp_workspace_size(const pinsage_mlp_t* mlp, int64_t n, size_
   if (st) return st;
   if (!bytes) return fail(PINSAGE_EINVAL, "bytes is NULL");
   if (n < 0) return fail(PINSAGE_EINVAL, "negative row count");
-  *bytes = mlp_ws(mlp, n);
+  *bytes = mlp_ws(mlp, n, true);
   return PINSAGE_OK;
 }
 
@@ -1293,12 +1344,13 @@ int pinsage_output_mlp(const pinsage_mlp_t* mlp, const void* h, int64_t n, void*
   if (n < 0) return fail(PINSAGE_EINVAL, "negative row count");
   if (n == 0) return PINSAGE_OK;
   if (!h || !z) return fail(PINSAGE_EINVAL, "h or z is NULL");
-  const size_t need = mlp_ws(mlp, n);
+  const size_t need = mlp_ws(mlp, n, false);
   if (!workspace || workspace_bytes < need)
     return fail(PINSAGE_EWORKSPACE, "workspace %zu bytes < required %zu", workspace_bytes, need);
   if (reinterpret_cast<uintptr_t>(workspace) % 256)
     return fail(PINSAGE_EINVAL, "workspace is not 256-byte aligned");
-  return run_mlp(mlp, h, nullptr, n, n, z, workspace, static_cast<hipStream_t>(stream));
+  return run_mlp(mlp, h, nullptr, n, n, z, workspace, workspace_bytes >= mlp_ws(mlp, n, true),
+                 static_cast<hipStream_t>(stream));
 }
 
 int pinsage_max_margin_loss(const void* zq, const void* zpos, int64_t B, const void* zneg,
@@ -1354,7 +1406,7 @@ struct MbPlan {
 
 int make_plan(const pinsage_graph_t* g, const pinsage_walk_params_t* w,
               const pinsage_layer_t* layers, int K, const pinsage_mlp_t* mlp, int64_t B,
-              int64_t n_neg, int64_t n_hard, MbPlan* p) {
+              int64_t n_neg, int64_t n_hard, bool pre, MbPlan* p) {
   const int64_t N = g->num_pins + g->num_boards;
   p->K = K;
   p->T = w->top_t;
@@ -1388,13 +1440,13 @@ int make_plan(const pinsage_graph_t* g, const pinsage_walk_params_t* w,
   p->pp = take((size_t)B * 4);
   size_t conv = 0;
   for (int k = 1; k <= K; ++k) {
-    const size_t c = convolve_ws(&layers[k - 1], p->U[k - 1], p->U[k]);
+    const size_t c = convolve_ws(&layers[k - 1], p->U[k - 1], p->U[k], pre);
     conv = c > conv ? c : conv;
   }
   p->conv = take(conv);
   if (mlp) {  // z of the targets' set, and the hidden activations of the output layers
     p->z = take((size_t)p->U[K] * mlp->d_out * elem_size(mlp->dtype));
-    p->mlp = take(mlp_ws(mlp, p->U[K]));
+    p->mlp = take(mlp_ws(mlp, p->U[K], pre));
   }
   p->total = cur;
   return PINSAGE_OK;
@@ -1456,7 +1508,7 @@ int pinsage_minibatch_workspace_size(const pinsage_graph_t* graph,
   if (st) return st;
   if (!bytes) return fail(PINSAGE_EINVAL, "bytes is NULL");
   MbPlan p;
-  make_plan(graph, walk, layers, num_layers, mlp, num_pairs, num_negatives, num_hard, &p);
+  make_plan(graph, walk, layers, num_layers, mlp, num_pairs, num_negatives, num_hard, true, &p);
   *bytes = p.total;
   return PINSAGE_OK;
 }
@@ -1479,7 +1531,12 @@ int pinsage_minibatch_forward(const pinsage_graph_t* graph, const pinsage_walk_p
     return fail(PINSAGE_EINVAL, "hard_negatives is NULL with num_hard > 0");
   if (!x || !loss) return fail(PINSAGE_EINVAL, "x or loss is NULL");
   MbPlan p;
-  make_plan(graph, walk, layers, K, mlp, B, n_neg, n_hard, &p);
+  make_plan(graph, walk, layers, K, mlp, B, n_neg, n_hard, true, &p);
+  const bool pre = workspace_bytes >= p.total;
+  if (!pre) {
+    p = MbPlan{};
+    make_plan(graph, walk, layers, K, mlp, B, n_neg, n_hard, false, &p);
+  }
   if (!workspace || workspace_bytes < p.total)
     return fail(PINSAGE_EWORKSPACE, "workspace %zu bytes < required %zu", workspace_bytes,
                 p.total);
@@ -1579,10 +1636,10 @@ int pinsage_minibatch_forward(const pinsage_graph_t* graph, const pinsage_walk_p
     if (k == 1) {
       // h^(0) = x read in place: P rows are x[S^(0) pins], self rows x[S^(1)].
       st = run_layer(L, x, N, npins[0], set_of(0), &nb, set_of(1), ws + p.h[1], size[1], conv_ws,
-                     s);
+                     pre, s);
     } else {
       st = run_layer(L, ws + p.h[k - 1], size[k - 1], npins[k - 1], nullptr, &nb, self_of(k),
-                     ws + p.h[k], size[k], conv_ws, s);
+                     ws + p.h[k], size[k], conv_ws, pre, s);
     }
     if (st) return st;
   }
@@ -1592,7 +1649,7 @@ int pinsage_minibatch_forward(const pinsage_graph_t* graph, const pinsage_walk_p
   const unsigned char* zsrc = ws + p.h[K];
   int d = LK->d_out;
   if (mlp) {
-    if ((st = run_mlp(mlp, ws + p.h[K], nullptr, size[K], size[K], ws + p.z, ws + p.mlp, s)))
+    if ((st = run_mlp(mlp, ws + p.h[K], nullptr, size[K], size[K], ws + p.z, ws + p.mlp, pre, s)))
       return st;
     zsrc = ws + p.z;
     d = mlp->d_out;

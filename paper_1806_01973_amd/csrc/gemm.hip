@@ -20,13 +20,31 @@
 // 16 (resp. 8) rows of one LDS fragment read over distinct banks. Missing rows
 // and the K tail read a static zero row, so loads never branch.
 //
-// fp32 storage: v_mfma_f32_32x32x2_f32; step st of a chunk pairs half-wave h
-// with chunk column 8h + st (two 16-byte reads per fragment). bf16 storage:
-// v_mfma_f32_32x32x16_bf16 (gfx950); k-step ks takes vector 2ks + h. fp32
-// accumulation in both cases. The weight fragment is the MFMA's first
-// operand, so the accumulators hold C^T blocks: a lane owns one output row
-// and runs of 4 adjacent output columns, stored as one 8-byte (bf16) or
-// 16-byte (fp32) vector.
+// bf16 storage: v_mfma_f32_32x32x16_bf16 (gfx950); k-step ks of a chunk takes
+// vector 2ks + h in half-wave h. fp32 accumulation. The weight fragment is the
+// MFMA's first operand, so the accumulators hold C^T blocks: a lane owns one
+// output row and runs of 4 adjacent output columns, stored as one 8-byte (bf16)
+// or 16-byte (fp32) vector.
+//
+// fp32 storage: the matrix cores run bf16 16 times as fast as fp32, so every
+// operand is split exactly into three bf16 parts (split3) and the six products
+// of parts that reach fp32's last bits run as bf16 MFMAs, the leading one and
+// the five small ones in accumulators of their own. That is no less precise
+// than the fp32 MFMA it replaces: relative error (2-norm, against 64 bits) of a
+// K = 256 product 0.9e-7 against 2.8e-7, K = 512 1.3e-7 against 4.0e-7, K = 768
+// with the row norm 1.0e-7 against 2.9e-7 (each MFMA rounds the running sum
+// once per 16 columns instead of once per 2; with all six in one accumulator it
+// is 2.4e-7). What bounds it: the MFMAs (48% busy at K = 256) beside the VALU work of
+// the splits, 44 instructions per 8 x 64 values, which fill most issue slots
+// the MFMAs leave when each tile splits both operands; a wave therefore covers
+// 64 x 64 (64 accumulators of each kind, two waves per SIMD), the next chunk is
+// split among the current one's MFMAs, and products of many rows read weights
+// that one small kernel split beforehand (split_b_kernel, PRE). 1M rows, 256 ->
+// 512: 2.34 ms (112 TFLOP/s) with fp32 MFMAs, 1.77 with both operands split in
+// the tiles, 1.62 (162 TFLOP/s) with B split before; 512 -> 256: 2.20, 1.62, 1.48;
+// 1.2M rows of the W layer (768 -> 256, norm): 4.12, 2.83, 2.48 (190 TFLOP/s).
+// (The remainders as two-element bf16 dot products are fewer instructions, but
+// those run on the matrix pipe: 3.09 instead of 2.83.)
 //
 // Epilogue: + bias, + an optional addend matrix (the pooled neighbour term
 // when W is split, see run_layer), ReLU (optional without L2), store in the
@@ -60,8 +78,11 @@ constexpr int kGroupBytes = 1024;    // 16 rows x 64 bytes: one DMA instruction
 // Slot of 16-byte vector v of row r (r mod 16) inside the row's 64 bytes.
 __device__ __forceinline__ int vec_slot(int r, int v) { return v ^ (((r >> 1) ^ (r >> 3)) & 3); }
 
-template <bool BF16, int BM_, int BN_, int WAVES_M_, int WAVES_N_, bool L2_, int STAGES_>
+template <bool BF16, int BM_, int BN_, int WAVES_M_, int WAVES_N_, bool L2_, int STAGES_,
+          int WPE_ = 1, bool PRE_ = false>
 struct Cfg {
+  static constexpr bool PRE = PRE_;  // fp32: B arrives split (launch_split_b)
+  static constexpr int WPE = WPE_;  // waves per SIMD the register budget must allow
   static constexpr bool kBf16 = BF16;
   static constexpr bool kTwoSources = L2_;  // the W layer reads [h_self | n]
   static constexpr bool L2 = L2_;
@@ -75,16 +96,21 @@ struct Cfg {
   static constexpr int BK = kChunkRowBytes / ESZ; // K columns per chunk
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   static constexpr int TM = WM / 32, TN = WN / 32;
-  static constexpr int A_GROUPS = BM / 16;
-  static constexpr int GROUPS = (BM + BN) / 16;
+  // A stage: A_GROUPS groups of 16 A rows, then B's groups (of 16 rows, or the
+  // 32-row block parts of split B). Each wave issues the same number of DMAs;
+  // the groups that a rounded-up split adds take the zero row. With split B, a
+  // wave's first A_DPW DMAs are A's and the rest B's.
+  static constexpr int B_GROUPS = PRE ? BN / 32 * 3 : BN / 16;
+  static constexpr int A_GROUPS = PRE ? (BM / 16 + NWAVES - 1) / NWAVES * NWAVES : BM / 16;
+  static constexpr int GROUPS = (A_GROUPS + B_GROUPS + NWAVES - 1) / NWAVES * NWAVES;
   static constexpr int DPW = GROUPS / NWAVES;     // DMA instructions per wave per chunk
+  static constexpr int ROW_DPW = PRE ? A_GROUPS / NWAVES : DPW;  // of them, row groups
   static constexpr int PENDING = (STAGES - 2) * DPW;
   static constexpr int STAGE_BYTES = GROUPS * kGroupBytes;
   static constexpr int RED_BYTES = L2 ? WAVES_N * BM * 4 : 0;
   static constexpr int BIAS_BYTES = BN * 4;
   static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + RED_BYTES + BIAS_BYTES;
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile is a multiple of 32x32");
-  static_assert(GROUPS % NWAVES == 0, "every wave issues the same DMA count");
   static_assert(STAGES >= 2 && PENDING <= 63, "vmcnt range");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of one workgroup");
 };
@@ -104,6 +130,14 @@ __device__ __forceinline__ void dma16(const void* g, uint32_t lds_base) {
                : "memory");
 }
 
+// The same with a wave-uniform base and a 32-bit byte offset per lane.
+__device__ __forceinline__ void dma16_base(const void* base, uint32_t off, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds_base), "v"(off), "s"(base)
+               : "memory");
+}
+
 // Waits until at most N vector-memory operations of this wave are in flight.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -115,11 +149,46 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
 }
 
+// fp32 operands on the bf16 matrix cores: x = h + m + l exactly, each part the
+// bf16 rounding of what the parts before it leave (8 + 8 + 8 significand bits
+// hold fp32's 24).
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+struct Split3 {
+  u32x4_t p[3];
+};
+__device__ __forceinline__ Split3 split3(const u32x4_t& u, const u32x4_t& v) {
+  Split3 s;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float x0 = __uint_as_float(q < 2 ? u[2 * q] : v[2 * q - 4]);
+    float x1 = __uint_as_float(q < 2 ? u[2 * q + 1] : v[2 * q - 3]);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const uint32_t w = pack_bf16x2(x0, x1);
+      s.p[t][q] = w;
+      if (t < 2) {
+        x0 -= __uint_as_float(w << 16);
+        x1 -= __uint_as_float(w & 0xFFFF0000u);
+      }
+    }
+  }
+  return s;
+}
+// Product t of the six that matter, smallest first: parts (2,0) (0,2) (1,1)
+// (1,0) (0,1) (0,0); the three left out are below 2^-25 of the product.
+__device__ __forceinline__ f32x16 mfma_split(const Split3& b, const Split3& a, int t,
+                                             const f32x16& c) {
+  constexpr int pb[6] = {2, 0, 1, 1, 0, 0}, pa[6] = {0, 2, 1, 0, 1, 0};
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b.p[pb[t]]),
+                                                 __builtin_bit_cast(bf16x8, a.p[pa[t]]), c, 0, 0,
+                                                 0);
+}
+
 template <typename C>
-__global__ __launch_bounds__(C::THREADS) void gemm_kernel(GemmLaunch a) {
+__global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) {
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, VEC = C::VEC;
   constexpr int TM = C::TM, TN = C::TN, THREADS = C::THREADS, ESZ = C::ESZ;
-  constexpr int DPW = C::DPW, STAGES = C::STAGES;
+  constexpr int DPW = C::DPW, ROW_DPW = C::ROW_DPW, STAGES = C::STAGES;
   // LDS: the stage ring, then the cross-wave row-norm partials and the
   // block's bias slice.
   __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS_BYTES];
@@ -151,15 +220,16 @@ __global__ __launch_bounds__(C::THREADS) void gemm_kernel(GemmLaunch a) {
   // rows that do not exist point at the zero row.
   const unsigned char* const zrow = reinterpret_cast<const unsigned char*>(g_zero_row);
   const int64_t k0b = (int64_t)a.K0 * ESZ;
-  const unsigned char* p0[DPW];
-  const unsigned char* p1[C::kTwoSources ? DPW : 1];
+  const int nb32 = (a.N + 31) / 32;  // 32-row blocks of split B
+  const unsigned char* p0[ROW_DPW];
+  const unsigned char* p1[C::kTwoSources ? ROW_DPW : 1];
 #pragma unroll
-  for (int d = 0; d < DPW; ++d) {
-    const int grp = wave * DPW + d;
+  for (int d = 0; d < ROW_DPW; ++d) {
+    const int grp = wave * ROW_DPW + d;
     const int rr = lane >> 2;
-    if (grp < C::A_GROUPS) {
+    if (C::PRE || grp < C::A_GROUPS) {
       const int64_t gr = m0 + grp * 16 + rr;
-      const bool in_m = gr < a.M;
+      const bool in_m = gr < a.M && grp < BM / 16;
       const int64_t src = !in_m ? -1 : (a.rowmap ? (int64_t)a.rowmap[gr] : gr);
       p0[d] = (src >= 0 && src < a.rows_a0)
                   ? static_cast<const unsigned char*>(a.A0) + src * a.lda0 * ESZ
@@ -198,14 +268,27 @@ __global__ __launch_bounds__(C::THREADS) void gemm_kernel(GemmLaunch a) {
     const int kk = kc * BK + kvec;
     const bool kin = kk < K;
     const int64_t off = (int64_t)kk * ESZ;
-    const uint32_t dst = smem_base + (uint32_t)((chunk % STAGES) * C::STAGE_BYTES) +
-                         (uint32_t)(wave * DPW * kGroupBytes);
+    const uint32_t dst = smem_base + (uint32_t)((chunk % STAGES) * C::STAGE_BYTES);
+    const uint32_t dst_rows = dst + (uint32_t)(wave * ROW_DPW * kGroupBytes);
 #pragma unroll
-    for (int d = 0; d < DPW; ++d) {
+    for (int d = 0; d < ROW_DPW; ++d) {
       const unsigned char* p;
       if constexpr (C::kTwoSources) p = (kk < a.K0 ? p0[d] : p1[d]) + off;
       else p = p0[d] + off;
-      dma16(kin ? p : zrow, __builtin_amdgcn_readfirstlane(dst + d * kGroupBytes));
+      dma16(kin ? p : zrow, __builtin_amdgcn_readfirstlane(dst_rows + d * kGroupBytes));
+    }
+    if constexpr (C::PRE) {
+      // 1 KB each of split B's chunk: 32-row block n0 / 32 + gb / 3, part gb % 3.
+      const unsigned char* const chunk_b =
+          static_cast<const unsigned char*>(a.Bs) + (int64_t)kc * nb32 * 3072;
+#pragma unroll
+      for (int d = 0; d < DPW - ROW_DPW; ++d) {
+        const int gb = wave * (DPW - ROW_DPW) + d;
+        const int blk = n0 / 32 * 3 + gb;
+        const bool in = chunk < nchunks && gb < C::B_GROUPS && blk < 3 * nb32;
+        dma16_base(in ? chunk_b + blk * 1024 : zrow, 16u * (uint32_t)lane,
+                   __builtin_amdgcn_readfirstlane(dst + (C::A_GROUPS + gb) * kGroupBytes));
+      }
     }
   };
 
@@ -229,33 +312,37 @@ __global__ __launch_bounds__(C::THREADS) void gemm_kernel(GemmLaunch a) {
   };
   const int fa_off = frag_off(a_base_row + row_in_blk);
   const int fb_off = C::A_GROUPS * kGroupBytes + frag_off(b_base_row + row_in_blk);
-  // Byte offset of the vector a lane reads in half-step hs.
+  // Byte offset of the vector a lane reads in half-step hs (bf16), or of the
+  // hs-th vector of its eight columns (fp32).
   auto vec_off = [&](int hs) __attribute__((always_inline)) {
     const int v = C::kBf16 ? 2 * hs + half : 2 * half + hs;
     return vec_slot(lane & 15, v) * 16;
   };
   const int voff0 = vec_off(0), voff1 = vec_off(1);
 
-  // A chunk is multiplied in two half-steps hs = 0, 1. bf16: half-step hs is
-  // the MFMA k-step hs, half-wave h reads column vector 2hs + h. fp32: MFMA
-  // steps 4hs .. 4hs+3, half-wave h reads vector 2h + hs (column 8h + st).
-  constexpr int FW = 4;  // 32-bit words per fragment per half-step
+  constexpr int FW = 4;  // 32-bit words per 16-byte vector
   typedef uint32_t frag_t __attribute__((ext_vector_type(FW)));
-  struct Frags {
-    frag_t a[TM], b[TN];
+  auto stage_of = [&](int chunk) __attribute__((always_inline)) {
+    return smem + (chunk % STAGES) * C::STAGE_BYTES;
   };
-  auto read_frags = [&](const unsigned char* stage, int hs, Frags& f)
-      __attribute__((always_inline)) {
-    const int v = hs ? voff1 : voff0;
+
+  if constexpr (C::kBf16) {
+    // A chunk is multiplied in two half-steps hs = 0, 1 (the MFMA k-steps);
+    // half-wave h reads column vector 2hs + h.
+    struct Frags {
+      frag_t a[TM], b[TN];
+    };
+    auto read_frags = [&](const unsigned char* stage, int hs, Frags& f)
+        __attribute__((always_inline)) {
+      const int v = hs ? voff1 : voff0;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-      f.a[i] = *reinterpret_cast<const frag_t*>(stage + fa_off + i * 2 * kGroupBytes + v);
+      for (int i = 0; i < TM; ++i)
+        f.a[i] = *reinterpret_cast<const frag_t*>(stage + fa_off + i * 2 * kGroupBytes + v);
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-      f.b[j] = *reinterpret_cast<const frag_t*>(stage + fb_off + j * 2 * kGroupBytes + v);
-  };
-  auto mfma_half = [&](const Frags& f) __attribute__((always_inline)) {
-    if constexpr (C::kBf16) {
+      for (int j = 0; j < TN; ++j)
+        f.b[j] = *reinterpret_cast<const frag_t*>(stage + fb_off + j * 2 * kGroupBytes + v);
+    };
+    auto mfma_half = [&](const Frags& f) __attribute__((always_inline)) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -263,55 +350,183 @@ __global__ __launch_bounds__(C::THREADS) void gemm_kernel(GemmLaunch a) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               __builtin_bit_cast(bf16x8, f.b[j]), __builtin_bit_cast(bf16x8, f.a[i]), acc[i][j],
               0, 0, 0);
-    } else {
+    };
+
+    // Ring protocol: chunks 0..STAGES-2 are in flight before the loop. Before
+    // the fragments of chunk c+1 are read, each wave waits for its DMAs of that
+    // chunk (STAGES - 2 younger chunks may stay in flight) and for its own LDS
+    // reads of chunk c, then a barrier makes all DMAs visible and frees chunk
+    // c's stage, which receives chunk c + STAGES. The half-step MFMAs issued
+    // just before the barrier keep the matrix pipe busy across it.
 #pragma unroll
-      for (int st = 0; st < 4; ++st)
+    for (int c = 0; c < STAGES - 1; ++c) issue(c);
+    wait_vmcnt<C::PENDING>();
+    lds_barrier();
+    issue(STAGES - 1);
+    Frags f0, f1;
+    read_frags(stage_of(0), 0, f0);
+    // The last chunk is peeled off so the loop body has no branch: every
+    // half-step's fragment reads then have a known count of younger reads.
+    // Scheduling barriers pin the order: fragment reads go out right before a
+    // half-step's 16 MFMAs that hide their latency.
+    for (int c = 0; c + 1 < nchunks; ++c) {
+      read_frags(stage_of(c), 1, f1);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(f0);
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vmcnt<C::PENDING>();
+      lds_barrier();
+      read_frags(stage_of(c + 1), 0, f0);
+      __builtin_amdgcn_sched_barrier(0);
+      issue(c + STAGES);
+      __builtin_amdgcn_sched_barrier(0);
+      mfma_half(f1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    read_frags(stage_of(nchunks - 1), 1, f1);
+    mfma_half(f0);
+    mfma_half(f1);
+  } else {
+    // fp32 storage: one k-step of 16 columns per chunk; half-wave h takes
+    // columns 8h .. 8h+7 (vectors 2h, 2h+1) and splits them into bf16 triples.
+    f32x16 small[TM][TN];  // the five products below the leading one
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) small[i][j][e] = 0.0f;
+    struct Parts {
+      Split3 a[TM], b[TN];
+    };
+    struct Raw {
+      frag_t a[TM][2], b[C::PRE ? 1 : TN][2];
+    };
+    auto read_raw = [&](const unsigned char* st, Raw& r) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        r.a[i][0] = *reinterpret_cast<const frag_t*>(st + fa_off + i * 2 * kGroupBytes + voff0);
+        r.a[i][1] = *reinterpret_cast<const frag_t*>(st + fa_off + i * 2 * kGroupBytes + voff1);
+      }
+      if constexpr (!C::PRE)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        r.b[j][0] = *reinterpret_cast<const frag_t*>(st + fb_off + j * 2 * kGroupBytes + voff0);
+        r.b[j][1] = *reinterpret_cast<const frag_t*>(st + fb_off + j * 2 * kGroupBytes + voff1);
+      }
+    };
+    auto read_parts = [&](const unsigned char* st, Parts& s) __attribute__((always_inline)) {
+      if constexpr (C::PRE)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int t = 0; t < 3; ++t)
+            s.b[j].p[t] = *reinterpret_cast<const u32x4_t*>(
+                st + C::A_GROUPS * kGroupBytes + ((wn * TN + j) * 3 + t) * 1024 + 16 * lane);
+    };
+    auto split_raw = [&](const Raw& r, Parts& s) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) s.a[i] = split3(r.a[i][0], r.a[i][1]);
+      if constexpr (!C::PRE)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) s.b[j] = split3(r.b[j][0], r.b[j][1]);
+    };
+    auto multiply = [&](const Parts& s) __attribute__((always_inline)) {
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                __uint_as_float(f.b[j][st]), __uint_as_float(f.a[i][st]), acc[i][j], 0, 0, 0);
-    }
-  };
-  auto stage_of = [&](int chunk) __attribute__((always_inline)) {
-    return smem + (chunk % STAGES) * C::STAGE_BYTES;
-  };
-
-  // Ring protocol: chunks 0..STAGES-2 are in flight before the loop. Before
-  // the fragments of chunk c+1 are read, each wave waits for its DMAs of that
-  // chunk (STAGES - 2 younger chunks may stay in flight) and for its own LDS
-  // reads of chunk c, then a barrier makes all DMAs visible and frees chunk
-  // c's stage, which receives chunk c + STAGES. The half-step MFMAs issued
-  // just before the barrier keep the matrix pipe busy across it.
+          for (int j = 0; j < TN; ++j) {
+            if (t < 5) small[i][j] = mfma_split(s.b[j], s.a[i], t, small[i][j]);
+            else acc[i][j] = mfma_split(s.b[j], s.a[i], t, acc[i][j]);
+          }
+    };
+    // Ring protocol: chunks 0..STAGES-1 are in flight before the loop. Step c
+    // waits for this wave's DMAs of chunk c + 1 (STAGES - 2 younger chunks stay
+    // in flight); the barrier makes everybody's visible and frees chunk c's
+    // stage (read and split in the step before) for chunk c + STAGES. Chunk
+    // c + 1 is read and split among the MFMAs of chunk c.
+    auto step = [&](int c, const Parts& cur, Parts& nxt) __attribute__((always_inline)) {
+      wait_vmcnt<C::PENDING>();
+      lds_barrier();
+      issue(c + STAGES);
+      Raw r;
+      read_raw(stage_of(c + 1), r);
+      read_parts(stage_of(c + 1), nxt);
+      __builtin_amdgcn_sched_barrier(0);
+      split_raw(r, nxt);
+      multiply(cur);
+      constexpr int kMfma = 6 * TM * TN, kValu = 44 * (TM + (C::PRE ? 0 : TN));
 #pragma unroll
-  for (int c = 0; c < STAGES - 1; ++c) issue(c);
-  wait_vmcnt<C::PENDING>();
-  lds_barrier();
-  issue(STAGES - 1);
-  Frags f0, f1;
-  read_frags(stage_of(0), 0, f0);
-  // The last chunk is peeled off so the loop body has no branch: every
-  // half-step's fragment reads then have a known count of younger reads.
-  // Scheduling barriers pin the order: fragment reads go out right before a
-  // half-step's 16 MFMAs that hide their latency.
-  for (int c = 0; c + 1 < nchunks; ++c) {
-    read_frags(stage_of(c), 1, f1);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_half(f0);
-    __builtin_amdgcn_sched_barrier(0);
-    wait_vmcnt<C::PENDING>();
+      for (int q = 0; q < kMfma; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                            // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, (kValu + kMfma - 1) / kMfma, 0);  // VALU
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    Parts s0, s1;
+#pragma unroll
+    for (int c = 0; c < STAGES; ++c) issue(c);
+    wait_vmcnt<C::PENDING + DPW>();
     lds_barrier();
-    read_frags(stage_of(c + 1), 0, f0);
-    __builtin_amdgcn_sched_barrier(0);
-    issue(c + STAGES);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_half(f1);
-    __builtin_amdgcn_sched_barrier(0);
+    {
+      Raw r;
+      read_raw(stage_of(0), r);
+      read_parts(stage_of(0), s0);
+      split_raw(r, s0);
+    }
+    // An odd chunk count multiplies one more chunk, all zeros.
+    for (int c = 0; c < nchunks; c += 2) {
+      step(c, s0, s1);
+      step(c + 1, s1, s0);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
+    // Rows the split does not cover: an infinity (or a value that rounds to
+    // one) leaves NaN parts, and values below about 2^-110 lose their last
+    // part. Either shows in the lane's results, which are then summed again in
+    // plain fp32, a row at a time.
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      float probe = 0.0f, big = 0.0f;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          probe = fmaf(acc[i][j][e], 0.0f, probe);  // NaN unless all are finite
+          big = fmaxf(big, fabsf(acc[i][j][e]));
+        }
+      if (probe == 0.0f && (big == 0.0f || big >= 0x1p-64f)) continue;
+      const int64_t r = m0 + a_base_row + i * 32 + row_in_blk;
+      const int64_t src = r >= a.M ? -1 : (a.rowmap ? (int64_t)a.rowmap[r] : r);
+      const float* const ra = src >= 0 && src < a.rows_a0
+                                  ? static_cast<const float*>(a.A0) + src * a.lda0
+                                  : g_zero_row;
+      const float* const rb = C::kTwoSources && a.A1 && r < a.M
+                                  ? static_cast<const float*>(a.A1) + r * a.lda1 - a.K0
+                                  : g_zero_row;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+#pragma unroll 1
+      for (int k = 0; k < K; ++k) {
+        const float x = k < a.K0 ? ra[k] : rb[k];
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int col = n0 + b_base_row + j * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+            const float y =
+                col < a.N ? static_cast<const float*>(a.B)[(int64_t)col * ldb + k] : 0.0f;
+            acc[i][j][e] = fmaf(x, y, acc[i][j][e]);
+          }
+      }
+    }
   }
-  read_frags(stage_of(nchunks - 1), 1, f1);
-  mfma_half(f0);
-  mfma_half(f1);
   wait_vmcnt<0>();  // drain the zero-row DMAs issued past the end
   __syncthreads();  // bias slice (and, below, row partials) visible
 
@@ -322,21 +537,45 @@ __global__ __launch_bounds__(C::THREADS) void gemm_kernel(GemmLaunch a) {
   // columns past N have zero weights and zero bias, so they stay zero.
   // Row bands are finished one at a time to keep few accumulators live.
   auto c0 = [&](int j, int g) __attribute__((always_inline)) { return b_base_row + j * 32 + 8 * g + 4 * half; };
-  // bf16 tiles that fit in the (now free) stage ring are staged there, rows
-  // padded by 16 bytes, and leave as whole rows (16 bytes per lane) rather
-  // than as 8-byte pieces of 32 rows per store instruction. (Loading the
-  // addend tile the same way, in front of the epilogue, measured slower: its
-  // latency is then exposed.)
-  constexpr int TROW = BN * 2 + 16;
+  // The output leaves through the (now free) stage ring as whole rows, 16 bytes
+  // per lane, rows padded by 16 bytes, instead of as each lane's 4-column pieces
+  // of 32 rows per store instruction (measured neutral at 1M x 256 -> 512, and
+  // the addend's reads become whole rows too). bf16 tiles that fit are staged
+  // whole. (Loading the addend tile the same way, in
+  // front of the epilogue, measured slower: its latency is then exposed.)
+  constexpr int TROW = BN * ESZ + 16;
   constexpr bool kStaged = C::kBf16 && BM * TROW <= STAGES * C::STAGE_BYTES;
-  constexpr int PER_ROW = BN / 8;  // 16-byte pieces per tile row
+  constexpr int PER_ROW = BN / VEC;  // 16-byte pieces per tile row
   // + bias (+ addend), then ReLU unless disabled; the L2 epilogue always
   // follows a ReLU.
   const bool relu = a.relu || C::L2;
-  auto bias_relu = [&](int i) __attribute__((always_inline)) {
-    const int rt = a_base_row + i * 32 + row_in_blk;
-    const int64_t r = m0 + rt;
-    const bool add = a.addend != nullptr && r < a.M;
+  // A lane's four columns at byte `at` of a staged row.
+  auto put4 = [&](unsigned char* at, float v0, float v1, float v2, float v3)
+      __attribute__((always_inline)) {
+    if constexpr (C::kBf16)
+      *reinterpret_cast<uint2*>(at) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+    else
+      *reinterpret_cast<float4*>(at) = make_float4(v0, v1, v2, v3);
+  };
+  auto add4 = [&](const unsigned char* at, float (&x)[4]) __attribute__((always_inline)) {
+    if constexpr (C::kBf16) {
+      const uint2 v = *reinterpret_cast<const uint2*>(at);
+      x[0] += __uint_as_float(v.x << 16);
+      x[1] += __uint_as_float(v.x & 0xFFFF0000u);
+      x[2] += __uint_as_float(v.y << 16);
+      x[3] += __uint_as_float(v.y & 0xFFFF0000u);
+    } else {
+      const float4 v = *reinterpret_cast<const float4*>(at);
+      x[0] += v.x;
+      x[1] += v.y;
+      x[2] += v.z;
+      x[3] += v.w;
+    }
+  };
+  // acc[i] = its band + bias + addend (lane_row: the addend's row of this
+  // lane, shifted to column 0 of the tile; null = none), ReLU; returns the lane's sum of squares.
+  auto finish_band = [&](int i, const unsigned char* lane_row) __attribute__((always_inline)) {
+    float s = 0.0f;
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -344,187 +583,110 @@ __global__ __launch_bounds__(C::THREADS) void gemm_kernel(GemmLaunch a) {
         const float4 bv = *reinterpret_cast<const float4*>(bias_s + c0(j, g));
         float x[4] = {acc[i][j][4 * g + 0] + bv.x, acc[i][j][4 * g + 1] + bv.y,
                       acc[i][j][4 * g + 2] + bv.z, acc[i][j][4 * g + 3] + bv.w};
-        const int c = n0 + c0(j, g);
-        if (add && c < a.N) {
-          const int64_t o = r * a.N + c;
-          if constexpr (C::kBf16) {
-            const uint2 v = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(a.addend) + o);
-            x[0] += __uint_as_float(v.x << 16);
-            x[1] += __uint_as_float(v.x & 0xFFFF0000u);
-            x[2] += __uint_as_float(v.y << 16);
-            x[3] += __uint_as_float(v.y & 0xFFFF0000u);
-          } else {
-            const float4 v = *reinterpret_cast<const float4*>(static_cast<const float*>(a.addend) + o);
-            x[0] += v.x;
-            x[1] += v.y;
-            x[2] += v.z;
-            x[3] += v.w;
-          }
-        }
+        if (lane_row && n0 + c0(j, g) < a.N) add4(lane_row + c0(j, g) * ESZ, x);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] = relu ? fmaxf(x[e], 0.0f) : x[e];
+        for (int e = 0; e < 4; ++e) {
+          const float y = relu ? fmaxf(x[e], 0.0f) : x[e];
+          acc[i][j][4 * g + e] = y;
+          s = fmaf(y, y, s);
+        }
       }
+    return s;
   };
-  auto store_band = [&](int i, float scale) __attribute__((always_inline)) {
-    const int rt = a_base_row + i * 32 + row_in_blk;  // row in the tile
-    const int64_t r = m0 + rt;
-    if (!kStaged && r >= a.M) return;
+  auto stage_band = [&](int i, unsigned char* lane_row, float scale)
+      __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int c = n0 + c0(j, g);
-        const float v0 = acc[i][j][4 * g] * scale, v1 = acc[i][j][4 * g + 1] * scale;
-        const float v2 = acc[i][j][4 * g + 2] * scale, v3 = acc[i][j][4 * g + 3] * scale;
-        if constexpr (kStaged) {
-          *reinterpret_cast<uint2*>(smem + rt * TROW + c0(j, g) * 2) =
-              make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
-        } else {
-          if (c >= a.N) continue;
-          const int64_t o = r * a.N + c;
-          if constexpr (C::kBf16) {
-            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.C) + o) =
-                make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
-          } else {
-            *reinterpret_cast<float4*>(static_cast<float*>(a.C) + o) =
-                make_float4(v0, v1, v2, v3);
-          }
-        }
-      }
+      for (int g = 0; g < 4; ++g)
+        put4(lane_row + c0(j, g) * ESZ, acc[i][j][4 * g] * scale, acc[i][j][4 * g + 1] * scale,
+             acc[i][j][4 * g + 2] * scale, acc[i][j][4 * g + 3] * scale);
   };
-  // Staged tile -> global, BN / 8 lanes per row.
-  auto flush_tile = [&]() __attribute__((always_inline)) {
-    if constexpr (kStaged) {
-      __syncthreads();
+  // `rows` staged rows -> global, BN / VEC lanes per row; row_of: their tile rows.
+  auto flush_rows = [&](int rows, auto row_of) __attribute__((always_inline)) {
 #pragma unroll 4
-      for (int e = tid; e < BM * PER_ROW; e += THREADS) {
-        const int rt = e / PER_ROW, ck = e % PER_ROW;
-        const int64_t r = m0 + rt;
-        const int c = n0 + 8 * ck;
-        if (r < a.M && c < a.N)
-          *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.C) + r * a.N + c) =
-              *reinterpret_cast<const uint4*>(smem + rt * TROW + 16 * ck);
-      }
+    for (int e = tid; e < rows * PER_ROW; e += THREADS) {
+      const int b = e / PER_ROW, ck = e % PER_ROW;
+      const int64_t r = m0 + row_of(b);
+      const int c = n0 + VEC * ck;
+      if (r < a.M && c < a.N)
+        *reinterpret_cast<uint4*>(static_cast<unsigned char*>(a.C) + (r * a.N + c) * ESZ) =
+            *reinterpret_cast<const uint4*>(smem + b * TROW + 16 * ck);
     }
   };
-
-  // bf16 L2 tiles too large to stage whole (512 columns): one row band at a
-  // time through the free stage ring, so the addend arrives and the output
-  // leaves as whole 16-byte row pieces (consecutive lanes, consecutive
-  // pieces of a row) instead of 8-byte pieces of 32 rows per instruction.
-  // Band i is row band i of every wave: tile rows WM wm' + 32 i + (0..31) for
-  // each wm'; band row b <-> tile row WM (b / 32) + 32 i + b % 32.
-  constexpr bool kBandLds = C::kBf16 && C::L2 && !kStaged;
-  constexpr int BROWS = 32 * C::WAVES_M;
-  static_assert(!kBandLds || BROWS * TROW <= STAGES * C::STAGE_BYTES, "a band fits the ring");
-  auto band_row = [&](int i, int b) __attribute__((always_inline)) {
-    return (b >> 5) * C::WM + 32 * i + (b & 31);
+  // The addend's row of this lane for band i, in memory.
+  auto addend_row = [&](int i) __attribute__((always_inline)) {
+    const int64_t r = m0 + a_base_row + i * 32 + row_in_blk;
+    return a.addend && r < a.M
+               ? static_cast<const unsigned char*>(a.addend) + (r * a.N + n0) * ESZ
+               : nullptr;
+  };
+  // Row norm: the lane's columns, its partner half-wave (lane ^ 32), then the
+  // WAVES_N waves of the row band in a fixed order through LDS.
+  auto put_partial = [&](int i, float s) __attribute__((always_inline)) {
+    s += __shfl_xor(s, 32);
+    if (half == 0) red[wn * BM + a_base_row + i * 32 + row_in_blk] = s;
+  };
+  auto row_scale = [&](int i) __attribute__((always_inline)) {
+    const int r = a_base_row + i * 32 + row_in_blk;
+    float ss = 0.0f;
+#pragma unroll
+    for (int w = 0; w < C::WAVES_N; ++w) ss += red[w * BM + r];
+    return ss > 0.0f ? 1.0f / sqrtf(ss) : 0.0f;
   };
 
-  if constexpr (!C::L2) {
+  if constexpr (kStaged) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      bias_relu(i);
-      store_band(i, 1.0f);
+      const float s = finish_band(i, addend_row(i));
+      if constexpr (C::L2) put_partial(i, s);
     }
-    flush_tile();
-  } else if constexpr (kBandLds) {
-    const int b_lane = wm * 32 + row_in_blk;  // this lane's row within a band
+    if constexpr (C::L2) __syncthreads();
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      // The band's addend rows into LDS (rows past M read as zeros).
-      if (a.addend) {
-#pragma unroll 4
-        for (int e = tid; e < BROWS * PER_ROW; e += THREADS) {
-          const int b = e / PER_ROW, ck = e % PER_ROW;
-          const int64_t r = m0 + band_row(i, b);
-          const int c = n0 + 8 * ck;
-          uint4 v = make_uint4(0u, 0u, 0u, 0u);
-          if (r < a.M && c < a.N)
-            v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.addend) + r * a.N + c);
-          *reinterpret_cast<uint4*>(smem + b * TROW + 16 * ck) = v;
-        }
-      }
-      __syncthreads();
-      // + bias + addend, ReLU, and the row's partial sum of squares.
-      float s = 0.0f;
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float4 bv = *reinterpret_cast<const float4*>(bias_s + c0(j, g));
-          float x[4] = {acc[i][j][4 * g + 0] + bv.x, acc[i][j][4 * g + 1] + bv.y,
-                        acc[i][j][4 * g + 2] + bv.z, acc[i][j][4 * g + 3] + bv.w};
-          if (a.addend) {
-            const uint2 v = *reinterpret_cast<const uint2*>(smem + b_lane * TROW + c0(j, g) * 2);
-            x[0] += __uint_as_float(v.x << 16);
-            x[1] += __uint_as_float(v.x & 0xFFFF0000u);
-            x[2] += __uint_as_float(v.y << 16);
-            x[3] += __uint_as_float(v.y & 0xFFFF0000u);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] = fmaxf(x[e], 0.0f);
-        }
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) s = fmaf(acc[i][j][e], acc[i][j][e], s);
-      s += __shfl_xor(s, 32);
-      if (half == 0) red[wn * BM + a_base_row + i * 32 + row_in_blk] = s;
-      __syncthreads();  // partial sums visible; every addend read of the band done
-      {
-        const int r = a_base_row + i * 32 + row_in_blk;
-        float ss = 0.0f;
-#pragma unroll
-        for (int w = 0; w < C::WAVES_N; ++w) ss += red[w * BM + r];
-        const float scale = ss > 0.0f ? 1.0f / sqrtf(ss) : 0.0f;
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const float v0 = acc[i][j][4 * g] * scale, v1 = acc[i][j][4 * g + 1] * scale;
-            const float v2 = acc[i][j][4 * g + 2] * scale, v3 = acc[i][j][4 * g + 3] * scale;
-            *reinterpret_cast<uint2*>(smem + b_lane * TROW + c0(j, g) * 2) =
-                make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
-          }
-      }
-      __syncthreads();
-#pragma unroll 4
-      for (int e = tid; e < BROWS * PER_ROW; e += THREADS) {
-        const int b = e / PER_ROW, ck = e % PER_ROW;
-        const int64_t r = m0 + band_row(i, b);
-        const int c = n0 + 8 * ck;
-        if (r < a.M && c < a.N)
-          *reinterpret_cast<uint4*>(static_cast<uint16_t*>(a.C) + r * a.N + c) =
-              *reinterpret_cast<const uint4*>(smem + b * TROW + 16 * ck);
-      }
-      __syncthreads();  // the staged band is read before the next band's addend lands
-    }
-  } else {
-    // Sum of squares of each row: over the lane's columns, then its partner
-    // half-wave (lane ^ 32), then the WAVES_N waves of the row band in a
-    // fixed order through LDS.
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      bias_relu(i);
-      float s = 0.0f;
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) s = fmaf(acc[i][j][e], acc[i][j][e], s);
-      s += __shfl_xor(s, 32);
-      if (half == 0) red[wn * BM + a_base_row + i * 32 + row_in_blk] = s;
-    }
+    for (int i = 0; i < TM; ++i)
+      stage_band(i, smem + (a_base_row + i * 32 + row_in_blk) * TROW,
+                 C::L2 ? row_scale(i) : 1.0f);
     __syncthreads();
+    flush_rows(BM, [](int b) { return b; });
+  } else {
+    // One row band at a time. Band i is row band i of every wave: tile rows
+    // WM wm' + 32 i + (0..31) for each wm'; band row b <-> tile row
+    // WM (b / 32) + 32 i + b % 32. The addend of an L2 tile arrives the same
+    // way, as whole row pieces.
+    constexpr int BROWS = 32 * C::WAVES_M;
+    static_assert(BROWS * TROW <= STAGES * C::STAGE_BYTES, "a band fits the ring");
+    unsigned char* const lane_row = smem + (wm * 32 + row_in_blk) * TROW;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int r = a_base_row + i * 32 + row_in_blk;
-      float ss = 0.0f;
-#pragma unroll
-      for (int w = 0; w < C::WAVES_N; ++w) ss += red[w * BM + r];
-      store_band(i, ss > 0.0f ? 1.0f / sqrtf(ss) : 0.0f);
+      auto band_row = [&](int b) __attribute__((always_inline)) {
+        return (b >> 5) * C::WM + 32 * i + (b & 31);
+      };
+      if constexpr (C::L2) {
+        if (a.addend) {
+#pragma unroll 4
+          for (int e = tid; e < BROWS * PER_ROW; e += THREADS) {
+            const int b = e / PER_ROW, ck = e % PER_ROW;
+            const int64_t r = m0 + band_row(b);
+            const int c = n0 + VEC * ck;
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (r < a.M && c < a.N)
+              v = *reinterpret_cast<const uint4*>(static_cast<const unsigned char*>(a.addend) +
+                                                  (r * a.N + c) * ESZ);
+            *reinterpret_cast<uint4*>(smem + b * TROW + 16 * ck) = v;
+          }
+          __syncthreads();
+        }
+        put_partial(i, finish_band(i, a.addend ? lane_row : nullptr));
+        __syncthreads();  // partial sums visible; every addend read of the band done
+        stage_band(i, lane_row, row_scale(i));
+      } else {
+        finish_band(i, addend_row(i));
+        stage_band(i, lane_row, 1.0f);
+      }
+      __syncthreads();
+      flush_rows(BROWS, band_row);
+      __syncthreads();  // the staged band is read before the next one lands
     }
-    flush_tile();
   }
 }
 
@@ -806,6 +968,32 @@ __global__ __launch_bounds__(C::THREADS) void gemm_rs_kernel(GemmLaunch a) {
   }
 }
 
+// Bs: B [N][K] (row stride ldb) as bf16 triples in the order the fp32 kernel's
+// MFMAs read them: [k-step of 16][32-row block][part][lane] x 16 bytes, lane l
+// holding columns 8 (l / 32) .. + 7 of row l % 32; rows past N are zero.
+__global__ void split_b_kernel(const float* __restrict__ B, int64_t ldb, int N, int K,
+                               u32x4_t* __restrict__ Bs) {
+  const int nb32 = (N + 31) / 32;
+  const int64_t total = (int64_t)(K / 16) * nb32 * 64;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
+       e += (int64_t)gridDim.x * blockDim.x) {
+    const int lane = (int)(e & 63);
+    const int64_t blk = e >> 6;
+    const int nb = (int)(blk % nb32), ks = (int)(blk / nb32);
+    const int row = 32 * nb + (lane & 31);
+    u32x4_t u = {0u, 0u, 0u, 0u}, v = u;
+    if (row < N) {
+      const u32x4_t* src =
+          reinterpret_cast<const u32x4_t*>(B + row * ldb + 16 * ks + 8 * (lane >> 5));
+      u = src[0];
+      v = src[1];
+    }
+    const Split3 s = split3(u, v);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) Bs[(blk * 3 + t) * 64 + lane] = s.p[t];
+  }
+}
+
 // The register-staged kernel covers bf16 launches with one A source, no row
 // map, no addend and no L2 epilogue, and rows whose byte strides keep 16-byte
 // vectors aligned.
@@ -846,42 +1034,42 @@ hipError_t launch_cfg(const GemmLaunch& a, hipStream_t s) {
 #define PINSAGE_CFG_Q_BF16 Cfg<true, 256, 256, 2, 2, false, 4>
 #endif
 #ifndef PINSAGE_CFG_Q_F32
-#define PINSAGE_CFG_Q_F32 Cfg<false, 256, 256, 4, 4, false, 4>
+#define PINSAGE_CFG_Q_F32 Cfg<false, 128, 128, 2, 2, false, PRE ? 3 : 4, 2, PRE>
 #endif
 #ifndef PINSAGE_CFG_W256_BF16
 #define PINSAGE_CFG_W256_BF16 Cfg<true, 128, 256, 2, 4, true, 3>
 #endif
 #ifndef PINSAGE_CFG_W256_F32
-#define PINSAGE_CFG_W256_F32 Cfg<false, 128, 256, 2, 4, true, 3>
+#define PINSAGE_CFG_W256_F32 Cfg<false, PRE ? 128 : 64, 256, PRE ? 2 : 1, 4, true, 3, 2, PRE>
 #endif
 #ifndef PINSAGE_CFG_W512_BF16
 #define PINSAGE_CFG_W512_BF16 Cfg<true, 128, 512, 2, 4, true, 3>
 #endif
-#ifndef PINSAGE_CFG_W512_F32
-#define PINSAGE_CFG_W512_F32 Cfg<false, 128, 512, 2, 4, true, 3>
-#endif
 
-template <bool BF16>
-hipError_t launch_typed(const GemmLaunch& a, hipStream_t s) {
-  if (!a.l2norm) {  // Q transform and the neighbour half of W share the tiles
-    if constexpr (BF16) return launch_cfg<PINSAGE_CFG_Q_BF16>(a, s);
-    else return launch_cfg<PINSAGE_CFG_Q_F32>(a, s);
-  }
+template <bool PRE>
+hipError_t launch_f32(const GemmLaunch& a, hipStream_t s) {
+  if (!a.l2norm) return launch_cfg<PINSAGE_CFG_Q_F32>(a, s);
+  if (a.N <= 64) return launch_cfg<Cfg<false, 128, 64, 4, 1, true, 4, 2, PRE>>(a, s);
+  if (a.N <= 128) return launch_cfg<Cfg<false, 128, 128, 2, 2, true, PRE ? 3 : 4, 2, PRE>>(a, s);
+  if (a.N <= 256) return launch_cfg<PINSAGE_CFG_W256_F32>(a, s);
+  if (a.N <= 512) return launch_cfg<Cfg<false, 64, 512, 1, 8, true, PRE ? 2 : 3, 2, PRE>>(a, s);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_bf16(const GemmLaunch& a, hipStream_t s) {
+  // Q transform and the neighbour half of W share the tiles.
+  if (!a.l2norm) return launch_cfg<PINSAGE_CFG_Q_BF16>(a, s);
   // The block must span every output column for the fused row norm.
-  if (a.N <= 64) return launch_cfg<Cfg<BF16, 128, 64, 4, 1, true, 4>>(a, s);
-  if (a.N <= 128) return launch_cfg<Cfg<BF16, 128, 128, 2, 2, true, 4>>(a, s);
-  if (a.N <= 256) {
-    if constexpr (BF16) return launch_cfg<PINSAGE_CFG_W256_BF16>(a, s);
-    else return launch_cfg<PINSAGE_CFG_W256_F32>(a, s);
-  }
-  if (a.N <= 512) {
-    if constexpr (BF16) return launch_cfg<PINSAGE_CFG_W512_BF16>(a, s);
-    else return launch_cfg<PINSAGE_CFG_W512_F32>(a, s);
-  }
+  if (a.N <= 64) return launch_cfg<Cfg<true, 128, 64, 4, 1, true, 4>>(a, s);
+  if (a.N <= 128) return launch_cfg<Cfg<true, 128, 128, 2, 2, true, 4>>(a, s);
+  if (a.N <= 256) return launch_cfg<PINSAGE_CFG_W256_BF16>(a, s);
+  if (a.N <= 512) return launch_cfg<PINSAGE_CFG_W512_BF16>(a, s);
   return hipErrorInvalidValue;
 }
 
 }  // namespace
+
+size_t split_b_bytes(int N, int K) { return (size_t)(K / 16) * ((N + 31) / 32) * 3072; }
 
 hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
@@ -889,7 +1077,14 @@ hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s) {
 #ifndef PINSAGE_GEMM_NO_RS
   if (use_rs(a)) return launch_rs(a, s);
 #endif
-  return a.bf16 ? launch_typed<true>(a, s) : launch_typed<false>(a, s);
+  if (a.bf16) return launch_bf16(a, s);
+  if (!a.Bs) return launch_f32<false>(a, s);
+  const int64_t units = (int64_t)((a.K0 + a.K1) / 16) * ((a.N + 31) / 32) * 64;
+  hipLaunchKernelGGL(split_b_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s,
+                     static_cast<const float*>(a.B), a.ldb ? a.ldb : (int64_t)a.K0 + a.K1, a.N,
+                     a.K0 + a.K1, static_cast<u32x4_t*>(a.Bs));
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_f32<true>(a, s);
 }
 
 }  // namespace pinsage

@@ -180,6 +180,9 @@ struct GemmLaunch {
   bool bf16;
   bool relu;
   bool l2norm;
+  // fp32: split_b_bytes(N, K0 + K1) of scratch for B as bf16 triples (written
+  // by the launch), or null (every tile then splits B itself; the same bits).
+  void* Bs = nullptr;
   int prof_class = -1;  // KernelClass for timing; -1: inferred from the epilogue
   // Rows of the whole product before row 0 of this launch (a multiple of 256).
   // Only the K-sweep rotation reads it, so a product split into row ranges
@@ -187,6 +190,7 @@ struct GemmLaunch {
   int64_t row_base = 0;
 };
 hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s);
+size_t split_b_bytes(int N, int K);
 
 // R[r] = ReLU(H[t(r)] Q^T + q) W_n^T for r in [0, rows), t(r) = rowmap[r] or
 // row0 + r (entries outside [0, rows_h) read as zero rows), bf16, with W_n'
