@@ -248,17 +248,14 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   }
   const int kvec = vec_slot(lane >> 2, lane & 3) * VEC;
   const int nchunks = (K + BK - 1) / BK;
-  // Tiles start their K sweep at different chunks (rotation by the tile's
-  // index in the whole product):
-  // rows of A and B sit at power-of-two strides, and blocks that all read the
-  // same K columns at once would pile onto a few L2 channels.
-#ifndef PINSAGE_GEMM_KSHIFT
-#define PINSAGE_GEMM_KSHIFT 0
-#endif
-  const int64_t abs_tile = tile + (a.row_base / BM) * tiles_n;
-  const int kshift = PINSAGE_GEMM_KSHIFT == 0 ? (int)(abs_tile % nchunks)
-                     : PINSAGE_GEMM_KSHIFT == 1 ? 0
-                     : (int)((abs_tile / tiles_n) % nchunks);
+  // The large bf16 tiles start their K sweep at different chunks (rotation by
+  // the tile's index in the whole product): rows of A and B sit at power-of-two
+  // strides, and blocks that all read the same K columns at once would pile onto
+  // a few L2 channels. The others (where it measured neutral) sum K in order, so
+  // that a row's bits do not depend on the tile shape its launch takes.
+  constexpr bool kRotate = C::kBf16 && BM * BN >= 128 * 256;
+  const int kshift =
+      kRotate ? (int)((tile + (a.row_base / BM) * tiles_n) % nchunks) : 0;
   // Issues the DMAs of the chunk-th chunk of this tile's sweep into its
   // stage. Sweep positions past the end read the zero row, which keeps the
   // in-flight count uniform for wait_vmcnt.
@@ -1029,7 +1026,6 @@ hipError_t launch_cfg(const GemmLaunch& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Tile shapes per (dtype, epilogue, output width).
 #ifndef PINSAGE_CFG_Q_BF16
 #define PINSAGE_CFG_Q_BF16 Cfg<true, 256, 256, 2, 2, false, 4>
 #endif
@@ -1046,25 +1042,66 @@ hipError_t launch_cfg(const GemmLaunch& a, hipStream_t s) {
 #define PINSAGE_CFG_W512_BF16 Cfg<true, 128, 512, 2, 4, true, 3>
 #endif
 
+// Tile shapes by dtype, epilogue, output width and how many tiles there are.
+// Below one large tile per CU (256) the chip is better filled by small ones: a
+// 2,500-row layer has 16 tiles of 128 x 128 but 32 of 64 x 64, and W 79 of 32 rows
+// instead of 20 of 128 (the 2,500-node job: 71 -> 57 us); 12,788 rows 256 -> 256 in
+// bf16 have 50 tiles of 256 x 256 and 200 of 128 x 128 (two such products and the
+// loss: 88 -> 67 us).
+constexpr int64_t kFewTiles = 256;
+inline int64_t tiles_of(const GemmLaunch& a, int bm, int bn) {
+  return ((a.M + bm - 1) / bm) * (int64_t)((a.N + bn - 1) / bn);
+}
+
+// Row-norm tiles span every output column.
+template <bool BF16>
+hipError_t launch_small_norm(const GemmLaunch& a, hipStream_t s) {
+  if (a.N <= 64) return launch_cfg<Cfg<BF16, 32, 64, 1, 2, true, 4>>(a, s);
+  if (a.N <= 128) return launch_cfg<Cfg<BF16, 32, 128, 1, 4, true, 4>>(a, s);
+  if (a.N <= 256) return launch_cfg<Cfg<BF16, 32, 256, 1, 8, true, 3>>(a, s);
+  return launch_cfg<Cfg<BF16, 32, 512, 1, 8, true, 3>>(a, s);
+}
+
 template <bool PRE>
 hipError_t launch_f32(const GemmLaunch& a, hipStream_t s) {
-  if (!a.l2norm) return launch_cfg<PINSAGE_CFG_Q_F32>(a, s);
+  if (!a.l2norm) {
+    // 128 x 64 where it leaves no empty half tile.
+    if (a.N <= 192 && (a.N + 63) / 64 % 2) return launch_cfg<Cfg<false, 128, 64, 4, 1, false, 4, 2, PRE>>(a, s);
+    return launch_cfg<PINSAGE_CFG_Q_F32>(a, s);
+  }
   if (a.N <= 64) return launch_cfg<Cfg<false, 128, 64, 4, 1, true, 4, 2, PRE>>(a, s);
   if (a.N <= 128) return launch_cfg<Cfg<false, 128, 128, 2, 2, true, PRE ? 3 : 4, 2, PRE>>(a, s);
   if (a.N <= 256) return launch_cfg<PINSAGE_CFG_W256_F32>(a, s);
-  if (a.N <= 512) return launch_cfg<Cfg<false, 64, 512, 1, 8, true, PRE ? 2 : 3, 2, PRE>>(a, s);
-  return hipErrorInvalidValue;
+  return launch_cfg<Cfg<false, 64, 512, 1, 8, true, PRE ? 2 : 3, 2, PRE>>(a, s);
 }
 
 hipError_t launch_bf16(const GemmLaunch& a, hipStream_t s) {
   // Q transform and the neighbour half of W share the tiles.
   if (!a.l2norm) return launch_cfg<PINSAGE_CFG_Q_BF16>(a, s);
-  // The block must span every output column for the fused row norm.
   if (a.N <= 64) return launch_cfg<Cfg<true, 128, 64, 4, 1, true, 4>>(a, s);
   if (a.N <= 128) return launch_cfg<Cfg<true, 128, 128, 2, 2, true, 4>>(a, s);
   if (a.N <= 256) return launch_cfg<PINSAGE_CFG_W256_BF16>(a, s);
-  if (a.N <= 512) return launch_cfg<PINSAGE_CFG_W512_BF16>(a, s);
-  return hipErrorInvalidValue;
+  return launch_cfg<PINSAGE_CFG_W512_BF16>(a, s);
+}
+
+// Few tiles of the large shapes; false when there are enough.
+bool launch_few(const GemmLaunch& a, hipStream_t s, hipError_t* e) {
+  if (a.l2norm) {
+    const int bm = a.bf16 || a.N <= 128 ? 128 : 64;
+    if (tiles_of(a, bm, 512) >= kFewTiles) return false;
+    *e = a.bf16 ? launch_small_norm<true>(a, s) : launch_small_norm<false>(a, s);
+    return true;
+  }
+  if (tiles_of(a, 128, 128) < kFewTiles) {
+    *e = a.bf16 ? launch_cfg<Cfg<true, 64, 64, 2, 2, false, 4>>(a, s)
+                : launch_cfg<Cfg<false, 64, 64, 2, 2, false, 4>>(a, s);
+    return true;
+  }
+  if (a.bf16 && tiles_of(a, 256, 256) < kFewTiles) {
+    *e = launch_cfg<Cfg<true, 128, 128, 2, 2, false, 4>>(a, s);
+    return true;
+  }
+  return false;
 }
 
 }  // namespace
@@ -1074,9 +1111,10 @@ size_t split_b_bytes(int N, int K) { return (size_t)(K / 16) * ((N + 31) / 32) *
 hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   ProfileScope prof(a.prof_class >= 0 ? a.prof_class : (a.l2norm ? kKGemmW : (a.relu ? kKGemmQ : kKGemmR)), s);
-#ifndef PINSAGE_GEMM_NO_RS
+  if (a.l2norm && a.N > 512) return hipErrorInvalidValue;
+  hipError_t few = hipSuccess;
+  if (launch_few(a, s, &few)) return few;
   if (use_rs(a)) return launch_rs(a, s);
-#endif
   if (a.bf16) return launch_bf16(a, s);
   if (!a.Bs) return launch_f32<false>(a, s);
   const int64_t units = (int64_t)((a.K0 + a.K1) / 16) * ((a.N + 31) / 32) * 64;
