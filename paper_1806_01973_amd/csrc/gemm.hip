@@ -60,12 +60,12 @@
 
 #include "device_util.h"
 #include "kernels.h"
+#include "split_device.h"
 
 namespace pinsage {
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // A row of zeros as long as the widest A row (d_in + m <= 16384 fp32): rows
 // that do not exist and the K tail read from here. Never written.
@@ -149,39 +149,11 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
 }
 
-// fp32 operands on the bf16 matrix cores: x = h + m + l exactly, each part the
-// bf16 rounding of what the parts before it leave (8 + 8 + 8 significand bits
-// hold fp32's 24).
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-struct Split3 {
-  u32x4_t p[3];
-};
-__device__ __forceinline__ Split3 split3(const u32x4_t& u, const u32x4_t& v) {
-  Split3 s;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    float x0 = __uint_as_float(q < 2 ? u[2 * q] : v[2 * q - 4]);
-    float x1 = __uint_as_float(q < 2 ? u[2 * q + 1] : v[2 * q - 3]);
-#pragma unroll
-    for (int t = 0; t < 3; ++t) {
-      const uint32_t w = pack_bf16x2(x0, x1);
-      s.p[t][q] = w;
-      if (t < 2) {
-        x0 -= __uint_as_float(w << 16);
-        x1 -= __uint_as_float(w & 0xFFFF0000u);
-      }
-    }
-  }
-  return s;
-}
-// Product t of the six that matter, smallest first: parts (2,0) (0,2) (1,1)
-// (1,0) (0,1) (0,0); the three left out are below 2^-25 of the product.
 __device__ __forceinline__ f32x16 mfma_split(const Split3& b, const Split3& a, int t,
                                              const f32x16& c) {
-  constexpr int pb[6] = {2, 0, 1, 1, 0, 0}, pa[6] = {0, 2, 1, 0, 1, 0};
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b.p[pb[t]]),
-                                                 __builtin_bit_cast(bf16x8, a.p[pa[t]]), c, 0, 0,
-                                                 0);
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b.p[split_b(t)]),
+                                                 __builtin_bit_cast(bf16x8, a.p[split_a(t)]), c, 0,
+                                                 0, 0);
 }
 
 template <typename C>
@@ -418,7 +390,7 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
         for (int j = 0; j < TN; ++j)
 #pragma unroll
           for (int t = 0; t < 3; ++t)
-            s.b[j].p[t] = *reinterpret_cast<const u32x4_t*>(
+            s.b[j].p[t] = *reinterpret_cast<const u32x4*>(
                 st + C::A_GROUPS * kGroupBytes + ((wn * TN + j) * 3 + t) * 1024 + 16 * lane);
     };
     auto split_raw = [&](const Raw& r, Parts& s) __attribute__((always_inline)) {
@@ -764,7 +736,6 @@ __global__ __launch_bounds__(C::THREADS) void gemm_rs_kernel(GemmLaunch a) {
   const int b_off0 = r0 * (int)a.ldb * 2 + v * 16, b_step = RSTEP * (int)a.ldb * 2;
   const int nchunks = (K + BK - 1) / BK;
 
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 stage_regs[2][LOADS];
   auto load_chunk = [&](int chunk, u32x4 (&r)[LOADS]) __attribute__((always_inline)) {
     // Bit 31 set (arithmetically, not by a select) sends the K tail past the
@@ -969,7 +940,7 @@ __global__ __launch_bounds__(C::THREADS) void gemm_rs_kernel(GemmLaunch a) {
 // MFMAs read them: [k-step of 16][32-row block][part][lane] x 16 bytes, lane l
 // holding columns 8 (l / 32) .. + 7 of row l % 32; rows past N are zero.
 __global__ void split_b_kernel(const float* __restrict__ B, int64_t ldb, int N, int K,
-                               u32x4_t* __restrict__ Bs) {
+                               u32x4* __restrict__ Bs) {
   const int nb32 = (N + 31) / 32;
   const int64_t total = (int64_t)(K / 16) * nb32 * 64;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
@@ -978,10 +949,10 @@ __global__ void split_b_kernel(const float* __restrict__ B, int64_t ldb, int N, 
     const int64_t blk = e >> 6;
     const int nb = (int)(blk % nb32), ks = (int)(blk / nb32);
     const int row = 32 * nb + (lane & 31);
-    u32x4_t u = {0u, 0u, 0u, 0u}, v = u;
+    u32x4 u = {0u, 0u, 0u, 0u}, v = u;
     if (row < N) {
-      const u32x4_t* src =
-          reinterpret_cast<const u32x4_t*>(B + row * ldb + 16 * ks + 8 * (lane >> 5));
+      const u32x4* src =
+          reinterpret_cast<const u32x4*>(B + row * ldb + 16 * ks + 8 * (lane >> 5));
       u = src[0];
       v = src[1];
     }
@@ -1120,7 +1091,7 @@ hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s) {
   const int64_t units = (int64_t)((a.K0 + a.K1) / 16) * ((a.N + 31) / 32) * 64;
   hipLaunchKernelGGL(split_b_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s,
                      static_cast<const float*>(a.B), a.ldb ? a.ldb : (int64_t)a.K0 + a.K1, a.N,
-                     a.K0 + a.K1, static_cast<u32x4_t*>(a.Bs));
+                     a.K0 + a.K1, static_cast<u32x4*>(a.Bs));
   const hipError_t e = hipGetLastError();
   return e != hipSuccess ? e : launch_f32<true>(a, s);
 }

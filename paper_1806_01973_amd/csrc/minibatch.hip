@@ -8,9 +8,12 @@
 // Everything is integer or fixed-order fp32, hence deterministic.
 #include "device_util.h"
 #include "kernels.h"
+#include "split_device.h"
 
 namespace pinsage {
 namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kScanThreads = 256;
 constexpr int kScanPerThread = 16;
@@ -130,152 +133,178 @@ __device__ __forceinline__ float load_elem(const void* base, int64_t i) {
   else return static_cast<const float*>(base)[i];
 }
 
-// Copies one d-wide row of a table (row id `row`, -1 = zero row) into LDS
-// as fp32; TPR threads share the row, thread c of them taking 16-byte vectors
-// c, c + TPR, ... (eight loads in flight before their stores). Rows whose
-// width is not a whole number of vectors go element by element.
-template <bool BF16, int TPR>
-__device__ __forceinline__ void stage_row(float* dst, const void* table, int64_t row, int d,
-                                          int c) {
-  constexpr int VE = BF16 ? 8 : 4;  // elements per 16-byte vector
-  constexpr int U = 8;
-  if (row < 0) {
-    for (int k = c; k < d; k += TPR) dst[k] = 0.0f;
-    return;
-  }
-  if (d % VE) {
-    for (int k = c; k < d; k += TPR) dst[k] = load_elem<BF16>(table, row * d + k);
-    return;
-  }
-  const uint4* src = reinterpret_cast<const uint4*>(
-      static_cast<const unsigned char*>(table) + (size_t)row * d * (BF16 ? 2 : 4));
-  const int nv = d / VE;
-  for (int v0 = c; v0 < nv; v0 += TPR * U) {
-    uint4 buf[U];
+// Elements k0 .. k0 + 7 of row `row` of a [rows][d] table as MFMA operand
+// parts: the bf16 values themselves, or fp32 values split exactly into three
+// bf16 parts. Zeros for row < 0 and past d. VEC: rows are whole 16-byte vectors.
+template <bool BF16, bool VEC>
+__device__ __forceinline__ auto load_parts(const void* table, int64_t row, int d, int k0) {
+  if constexpr (BF16) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (row < 0 || k0 >= d) return v;
+    const uint16_t* src = static_cast<const uint16_t*>(table) + row * d + k0;
+    if constexpr (VEC) {
+      v = *reinterpret_cast<const u32x4*>(src);
+    } else {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int v = v0 + TPR * u;
-      buf[u] = v < nv ? src[v] : make_uint4(0, 0, 0, 0);
+      for (int e = 0; e < 8; ++e)
+        if (k0 + e < d) v[e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int v = v0 + TPR * u;
-      if (v >= nv) break;
-      const uint32_t w[4] = {buf[u].x, buf[u].y, buf[u].z, buf[u].w};
-      float* o = dst + v * VE;
-      if constexpr (BF16) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          o[2 * i] = __uint_as_float(w[i] << 16);
-          o[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-        }
+    return v;
+  } else {
+    u32x4 u = {0u, 0u, 0u, 0u}, v = u;
+    if (row >= 0 && k0 < d) {
+      const float* src = static_cast<const float*>(table) + row * d + k0;
+      if constexpr (VEC) {  // d % 4 == 0
+        u = *reinterpret_cast<const u32x4*>(src);
+        if (k0 + 4 < d) v = *reinterpret_cast<const u32x4*>(src + 4);
       } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = __uint_as_float(w[i]);
+        for (int e = 0; e < 4; ++e) {
+          if (k0 + e < d) u[e] = __float_as_uint(src[e]);
+          if (k0 + 4 + e < d) v[e] = __float_as_uint(src[4 + e]);
+        }
       }
     }
+    return split3(u, v);
   }
 }
 
-// Eq. (1) per pair. A block of THREADS threads scores QB queries against the
-// negatives, NC at a time: the query rows and the chunk's negative rows sit
-// in LDS as fp32 with an odd row stride (rows read by one instruction fall in
-// distinct banks). The TPQ = THREADS / QB threads of query q take negatives
-// c, c + TPQ, ... of the chunk (NP each) and form each dot product over d in
-// index order, so one broadcast read of z_q serves NP products. A thread adds
-// its hinge terms in order, the TPQ threads of a query are summed by a fixed
-// butterfly, and chunk sums are added in chunk order. The positive score is a
-// partial dot per thread (indices c, c + TPQ, ...) summed by the same
-// butterfly.
-template <bool BF16, int THREADS, int QB, int NC, int DMAX>
-__global__ __launch_bounds__(THREADS) void loss_pairs_kernel(LossLaunch a) {
-  constexpr int TPQ = THREADS / QB;
-  constexpr int NP = NC / TPQ;
-  static_assert(TPQ <= 64 && NP * TPQ == NC && THREADS % NC == 0, "pair layout");
-  constexpr int S_MAX = DMAX + 1;
-  __shared__ float zq_s[QB * S_MAX];
-  __shared__ float zn_s[NC * S_MAX];
-  const int d = a.d;
-  const int S = d | 1;  // odd row stride >= d
-  const int t = threadIdx.x;
-  const int q = t / TPQ, c = t % TPQ;
+// Eq. (1) per pair. A block of 8 waves scores 16 queries against all the
+// negatives on the matrix cores (v_mfma_f32_16x16x32_bf16; fp32 storage as
+// split triples, six MFMAs per product): the queries' operand parts sit in LDS,
+// wave w takes negatives 16 (w + 8 i) .. + 15 and reads their rows straight
+// from memory as operands (the negatives are shared by every block and stay in
+// L2). A lane then holds one query's scores of 4 negatives; it adds its hinge
+// terms in order, the 4 lanes of a query are summed by a fixed butterfly and
+// the waves in order. The positive and the pair's own hard negatives are dot
+// products of 32 threads each, summed by a fixed butterfly.
+// What bounds it: the latency of the rows' reads. 2,048 pairs, 500 negatives,
+// d = 256, with the mean's launch: 16.8 us in bf16 and 27.1 in fp32, where fp32
+// FMAs from LDS took 47.0 and 49.7; with 4 hard negatives per pair 20.8 (50.6);
+// 4,096 pairs, 1,000 + 7 negatives, d = 512: 72 (340).
+// KS: most k-steps of 32 columns; TPQ threads per query.
+template <bool BF16, bool VEC, int KS>
+__global__ __launch_bounds__(512) void loss_pairs_kernel(LossLaunch a) {
+  constexpr int QB = 16, WAVES = 8, TPQ = 32;
+  constexpr int PARTS = BF16 ? 1 : 3;
+  constexpr int U = BF16 ? 8 : 4;  // k-steps in flight; KS is a multiple
+  __shared__ u32x4 qf[KS * PARTS * 64];
+  __shared__ float pos_s[QB], hard_s[QB], sum_s[WAVES][QB];
+  __shared__ int count_s[QB];
+  const int d = a.d, ksteps = (d + 31) / 32;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int64_t b0 = (int64_t)blockIdx.x * QB;
-  const int64_t b = b0 + q;
+  auto row_of = [](const int32_t* map, int64_t i) { return map ? (int64_t)map[i] : i; };
 
-  // Query rows of the block (zero rows for missing pairs or ids).
+  // Queries as operands: lane l of k-step ks holds row l % 16, columns
+  // 32 ks + 8 (l / 16) .. + 7 (zeros for missing pairs or ids).
+  for (int i = t; i < (ksteps + U - 1) / U * U * 64; i += 512) {
+    const int64_t b = b0 + (i & 15);
+    const int64_t row = b < a.B ? row_of(a.q_rows, b) : -1;
+    const auto f = load_parts<BF16, VEC>(a.zq, row, d, 32 * (i >> 6) + 8 * ((i >> 4) & 3));
+    if constexpr (BF16) {
+      qf[i] = f;
+    } else {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) qf[((i >> 6) * 3 + p) * 64 + (i & 63)] = f.p[p];
+    }
+  }
+  // Positive score and hard negatives of query t / 32.
   {
-    int64_t row = -1;
-    if (b < a.B) row = a.q_rows ? (int64_t)a.q_rows[b] : b;
-    stage_row<BF16, TPQ>(zq_s + q * S, a.zq, row, d, c);
+    const int q = t / TPQ, c = t % TPQ;
+    const int64_t b = b0 + q;
+    const int64_t qr = b < a.B ? row_of(a.q_rows, b) : -1;
+    auto dot = [&](const void* table, int64_t row) {
+      float s = 0.0f;
+      if (qr >= 0 && row >= 0)
+        for (int k = c; k < d; k += TPQ)
+          s = fmaf(load_elem<BF16>(a.zq, qr * d + k), load_elem<BF16>(table, row * d + k), s);
+#pragma unroll
+      for (int o = TPQ / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+      return s;
+    };
+    const float pos = dot(a.zpos, b < a.B ? row_of(a.pos_rows, b) : -1);
+    float hh = 0.0f;
+    int hv = 0;
+    if (b < a.B) {
+      for (int64_t j = 0; j < a.k_hard; ++j) {
+        const int64_t row = row_of(a.hard_rows, b * a.k_hard + j);
+        if (row < 0) continue;
+        const float h = dot(a.zhard, row) - pos + a.margin;
+        hh += h > 0.0f ? h : 0.0f;
+        ++hv;
+      }
+    }
+    if (c == 0) {
+      pos_s[q] = pos;
+      hard_s[q] = hh;
+      count_s[q] = hv;
+    }
   }
   __syncthreads();
-  // Positive score of query q.
-  float dp = 0.0f;
-  {
-    int64_t pr = -1;
-    if (b < a.B) pr = a.pos_rows ? (int64_t)a.pos_rows[b] : b;
-    if (pr >= 0)
-      for (int k = c; k < d; k += TPQ)
-        dp = fmaf(zq_s[q * S + k], load_elem<BF16>(a.zpos, pr * d + k), dp);
-  }
-#pragma unroll
-  for (int o = TPQ / 2; o >= 1; o >>= 1) dp += __shfl_xor(dp, o);
-  const float pos = dp;
 
-  constexpr int TPR = THREADS / NC;  // threads per staged negative row
+  const float shift = a.margin - pos_s[lane & 15];
   float acc = 0.0f;
-  for (int64_t c0 = 0; c0 < a.n_neg; c0 += NC) {
-    __syncthreads();  // previous chunk fully read
-    {
-      const int r = t / TPR;
-      const int64_t nn = c0 + r;
-      int64_t row = -1;
-      if (nn < a.n_neg) row = a.neg_rows ? (int64_t)a.neg_rows[nn] : nn;
-      stage_row<BF16, TPR>(zn_s + r * S, a.zneg, row, d, t % TPR);
+  for (int64_t n0 = 16 * wave; n0 < a.n_neg; n0 += 16 * WAVES) {
+    const int64_t n = n0 + (lane & 15);
+    const int64_t row = n < a.n_neg ? row_of(a.neg_rows, n) : -1;
+    f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f}, small = s;
+    // U k-steps' rows in flight before the first is multiplied.
+    for (int ks0 = 0; ks0 < ksteps; ks0 += U) {
+      decltype(load_parts<BF16, VEC>(a.zneg, row, d, 0)) f[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        f[u] = load_parts<BF16, VEC>(a.zneg, row, d, 32 * (ks0 + u) + 8 * (lane >> 4));
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const u32x4* q = qf + (ks0 + u) * PARTS * 64 + lane;
+        if constexpr (BF16) {
+          s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f[u]),
+                                                      __builtin_bit_cast(bf16x8, q[0]), s, 0, 0,
+                                                      0);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 6; ++i) {
+            f32x4& c = i < 5 ? small : s;
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, f[u].p[split_b(i)]),
+                __builtin_bit_cast(bf16x8, q[64 * split_a(i)]), c, 0, 0, 0);
+          }
+        }
+      }
     }
-    __syncthreads();
-    const float* zq = zq_s + q * S;
-    float dn[NP];
+    // Lane l: query l % 16, negatives n0 + 4 (l / 16) + 0..3.
 #pragma unroll
-    for (int j = 0; j < NP; ++j) dn[j] = 0.0f;
-    for (int k = 0; k < d; ++k) {
-      const float x = zq[k];
-#pragma unroll
-      for (int j = 0; j < NP; ++j) dn[j] = fmaf(x, zn_s[(c + TPQ * j) * S + k], dn[j]);
+    for (int r = 0; r < 4; ++r) {
+      const int64_t nr = n0 + 4 * (lane >> 4) + r;
+      float x = s[r] + small[r];
+      if constexpr (!BF16) {
+        // What the split does not cover (an infinity leaves NaN parts, tiny
+        // values lose their last part) is summed again in plain fp32.
+        const bool fine = fabsf(x) < INFINITY && (x == 0.0f || fabsf(x) >= 0x1p-64f);
+        if (!fine && nr < a.n_neg && b0 + (lane & 15) < a.B) {
+          const int64_t rn = row_of(a.neg_rows, nr), rq = row_of(a.q_rows, b0 + (lane & 15));
+          x = 0.0f;
+          if (rn >= 0 && rq >= 0)
+            for (int k = 0; k < d; ++k)
+              x = fmaf(load_elem<false>(a.zq, rq * d + k), load_elem<false>(a.zneg, rn * d + k), x);
+        }
+      }
+      const float h = x + shift;
+      acc += (nr < a.n_neg && h > 0.0f) ? h : 0.0f;
     }
-    float hc = 0.0f;
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-      const float h = dn[j] - pos + a.margin;
-      hc += (c0 + c + TPQ * j < a.n_neg && h > 0.0f) ? h : 0.0f;
-    }
-#pragma unroll
-    for (int o = TPQ / 2; o >= 1; o >>= 1) hc += __shfl_xor(hc, o);
-    acc += hc;
   }
-  // Pair b's own hard negatives (Sec. 3.3): thread c takes entries c, c + TPQ,
-  // ... and forms each dot product over d in index order from the row in
-  // memory; hinge sums and the count of present entries go through the same
-  // butterfly.
-  float hh = 0.0f;
-  int hv = 0;
-  for (int64_t j = c; j < a.k_hard; j += TPQ) {
-    int64_t row = -1;
-    if (b < a.B) row = a.hard_rows ? (int64_t)a.hard_rows[b * a.k_hard + j] : b * a.k_hard + j;
-    if (row < 0) continue;
-    const float* zq = zq_s + q * S;
-    float dn = 0.0f;
-    for (int k = 0; k < d; ++k) dn = fmaf(zq[k], load_elem<BF16>(a.zhard, row * d + k), dn);
-    const float h = dn - pos + a.margin;
-    hh += h > 0.0f ? h : 0.0f;
-    ++hv;
-  }
+  acc += __shfl_xor(acc, 16);
+  acc += __shfl_xor(acc, 32);
+  if (lane < QB) sum_s[wave][lane] = acc;
+  __syncthreads();
+  if (t < QB && b0 + t < a.B) {
+    float total = 0.0f;
 #pragma unroll
-  for (int o = TPQ / 2; o >= 1; o >>= 1) {
-    hh += __shfl_xor(hh, o);
-    hv += __shfl_xor(hv, o);
+    for (int w = 0; w < WAVES; ++w) total += sum_s[w][t];
+    a.per_pair[b0 + t] = (total + hard_s[t]) / (float)(a.n_neg + count_s[t]);
   }
-  if (c == 0 && b < a.B) a.per_pair[b] = (acc + hh) / (float)(a.n_neg + hv);
 }
 
 // Mean over pairs in a fixed order: strided per-thread sums, then a fixed tree.
@@ -370,22 +399,23 @@ hipError_t launch_gather_rows(const void* table, const int32_t* rows, int64_t n,
   return hipGetLastError();
 }
 
-template <int THREADS, int QB, int NC, int DMAX>
-void launch_loss_cfg(const LossLaunch& a, hipStream_t s) {
-  const dim3 grid((unsigned)((a.B + QB - 1) / QB)), block(THREADS);
-  if (a.bf16) hipLaunchKernelGGL((loss_pairs_kernel<true, THREADS, QB, NC, DMAX>), grid, block, 0,
-                                 s, a);
-  else hipLaunchKernelGGL((loss_pairs_kernel<false, THREADS, QB, NC, DMAX>), grid, block, 0, s, a);
+template <bool BF16, bool VEC>
+void launch_loss_typed(const LossLaunch& a, hipStream_t s) {
+  const dim3 grid((unsigned)((a.B + 15) / 16)), block(512);
+  // The queries' operands in LDS: up to 32 KB (bf16) or 96 KB (fp32, d = 1024).
+  if (a.d <= 256) hipLaunchKernelGGL((loss_pairs_kernel<BF16, VEC, 8>), grid, block, 0, s, a);
+  else if (a.d <= 512) hipLaunchKernelGGL((loss_pairs_kernel<BF16, VEC, 16>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((loss_pairs_kernel<BF16, VEC, 32>), grid, block, 0, s, a);
 }
 
 hipError_t launch_loss(const LossLaunch& a, hipStream_t s) {
   if (a.B <= 0) return hipSuccess;
   if (a.d < 1 || a.d > 1024 || a.B >= (1ll << 32)) return hipErrorInvalidValue;
   ProfileScope prof(kKLoss, s);
-  // LDS per block: (QB + NC) * (DMAX + 1) * 4 bytes <= 148 KB.
-  if (a.d <= 256) launch_loss_cfg<256, 8, 128, 256>(a, s);
-  else if (a.d <= 512) launch_loss_cfg<256, 8, 64, 512>(a, s);
-  else launch_loss_cfg<128, 4, 32, 1024>(a, s);
+  // Whole-vector rows: operands load as 16 bytes per lane, else by element.
+  const bool vec = a.d % (a.bf16 ? 8 : 4) == 0;
+  if (a.bf16) vec ? launch_loss_typed<true, true>(a, s) : launch_loss_typed<true, false>(a, s);
+  else vec ? launch_loss_typed<false, true>(a, s) : launch_loss_typed<false, false>(a, s);
   hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(256), 0, s, a.per_pair, a.B, a.loss);
   return hipGetLastError();
 }

@@ -1,0 +1,53 @@
+"""Max-margin loss at the edges of its tiles: 16 queries per block, 16 negatives per wave,
+k-steps of 32 columns in groups, rows that are not whole 16-byte vectors.
+
+Against 64 bits: a hinge term moves by at most the errors of its two scores, each
+(d + 8) 2^-24 of the summed magnitudes (fp32 accumulation, exact operands)."""
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,n,k,d", [(1, 1, 0, 1), (16, 16, 1, 32), (17, 15, 3, 33), (15, 129, 0, 31),
+                                     (33, 17, 2, 136), (40, 130, 1, 257), (18, 40, 1, 512),
+                                     (3, 300, 33, 520), (19, 31, 2, 1000)])
+def test_loss_at_tile_edges(dtype, B, n, k, d):
+    import paper_1806_01973_amd as ps
+    print(f"[case] loss {dtype} B={B} n={n} k={k} d={d}", flush=True)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator().manual_seed(B + d)
+    rows = lambda *s: torch.randn(s, generator=gen).mul_(d ** -0.5).to(dt)
+    q, p, ng = rows(B, d), rows(B, d), rows(n, d)
+    h = rows(B, k, d) if k else None
+    loss, per = ps.max_margin_loss(q.cuda(), p.cuda(), ng.cuda(), 0.1,
+                                   h.cuda() if k else None)
+    Q, P, N = q.double(), p.double(), ng.double()
+    s = torch.cat([Q @ N.t()] + ([(Q[:, None] * h.double()).sum(2)] if k else []), 1)
+    mag = torch.cat([Q.abs() @ N.abs().t()] + ([(Q.abs()[:, None] * h.double().abs()).sum(2)] if k else []), 1)
+    pos, pmag = (Q * P).sum(1, keepdim=True), (Q.abs() * P.abs()).sum(1, keepdim=True)
+    ref = torch.relu(s - pos + 0.1).mean(1)
+    tol = (d + 8) * 2.0 ** -24 * (mag + pmag).mean(1) + (n + k + 8) * 2.0 ** -24 * (ref + 0.1)
+    assert ((per.double().cpu() - ref).abs() <= tol).all()
+    assert abs(float(loss) - float(ref.mean())) <= float(tol.mean()) + 2e-6 * float(ref.mean())
+
+
+def test_loss_with_infinite_and_huge_rows():
+    import paper_1806_01973_amd as ps
+    gen = torch.Generator().manual_seed(2)
+    q, p, ng = (torch.randn((20, 64), generator=gen) for _ in range(3))
+    q[:, 5] = q[:, 5].abs() + 0.1
+    ng[3, 5] = -3.4e38  # a score far below every margin
+    ng[4, 5] = 3.4e38   # rounds to infinity in bf16; a huge finite hinge
+    ng[4, 6:] = 0.0
+    loss, per = ps.max_margin_loss(q.cuda(), p.cuda(), ng.cuda(), 0.1)
+    s = q.double() @ ng.double().t() - (q.double() * p.double()).sum(1, keepdim=True) + 0.1
+    ref = torch.relu(s).mean(1)
+    fine = s.amax(1) < 3e38  # the scores themselves fit fp32
+    assert fine.any()
+    assert torch.allclose(per.double().cpu()[fine], ref[fine], rtol=1e-5)
+    ng[4, 5] = float("inf")
+    _, per = ps.max_margin_loss(q.cuda(), p.cuda(), ng.cuda(), 0.1)
+    assert torch.isinf(per).all()
