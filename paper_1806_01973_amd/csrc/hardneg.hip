@@ -5,16 +5,22 @@
 // random.
 //
 // One workgroup of 1024 threads owns one query at a time (grid-stride over
-// queries); everything stays in LDS (about 2 x 4 B per visit slot):
-//   1. walks: thread t runs walks t, t + 1024, ..., two at a time; walk w
+// queries); everything stays in LDS (4.25 B per visit slot) and 64 registers, so
+// that two workgroups share a CU and one's sorts (VALU work) run under the
+// other's walks (random reads, which bound the kernel): 2,048 queries of 4,096 x 4
+// landings take 1.16 ms, 1.03 of it walks, where one workgroup per CU with a
+// second table of 4 B per slot for the ranked ids took 1.27. No such table: the
+// repeated pins are at most half the slots, so their keys and ids fit the sorted
+// visits' space, and a draw of a pin visited once is written by the thread that
+// holds it in registers.
+//   1. walks: thread t runs walks t, t + 1024, ...; walk w
 //      writes its pin landings into slots [w*hops, (w+1)*hops); the rest of
 //      the slots is empty;
 //   2. the visit ids are sorted (bitonic network: a register sort per wave,
 //      then merges across waves through LDS), so equal ids become runs;
-//   3. runs become distinct pins with visit counts, numbered d in ascending
-//      id order. Pins seen once rank last, in id order, so they go straight
-//      to their rank positions; pins seen more than once (few) get the key
-//      ((0xFFFF - count) << 16) | p, p their number among those pins;
+//   3. runs become distinct pins with visit counts, in ascending id order.
+//      Pins seen once rank last, in id order; pins seen more than once (few)
+//      get the key ((0xFFFF - count) << 16) | p, p their number among those;
 //   4. sorting those keys ranks the repeated pins by count descending, then
 //      id ascending, ahead of the single-visit pins;
 //   5. draw j: word 0 of Philox4x32-10 at counter (q, j, 0, 1) under the walk
@@ -31,10 +37,8 @@ using namespace walkdev;
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / kWave;
-#ifndef PINSAGE_HN_WALKERS
-#define PINSAGE_HN_WALKERS 2
-#endif
-constexpr int kWalkers = PINSAGE_HN_WALKERS;  // walks in flight per thread
+// Walks in flight per thread of a workgroup that has its CU to itself.
+constexpr int kAloneWalkers = 2;
 
 // LDS word of element i in a sort of kThreads * E keys: one pad word after
 // every E elements, so that lanes storing or loading their E consecutive
@@ -168,6 +172,20 @@ __device__ __forceinline__ int block_exclusive_sum(int v, int wave, int lane, in
   return before + incl - v;
 }
 
+// Exclusive prefix maximum of v >= -1 over the block in thread order (-1 for
+// the first thread). Contains barriers (every thread must call it).
+__device__ __forceinline__ int block_exclusive_max(int v, int wave, int lane, int* wave_tot) {
+  const int incl = wave_inclusive_max(v, lane);
+  if (lane == kWave - 1) wave_tot[wave] = incl;
+  __syncthreads();
+  int before = -1;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) before = imax(before, w < wave ? wave_tot[w] : -1);
+  __syncthreads();  // wave_tot is reused by the next call
+  const int up = __shfl_up(incl, 1);
+  return lane == 0 ? before : imax(before, up);
+}
+
 // MurmurHash3's 32-bit finaliser (a bijection with good avalanche).
 __device__ __forceinline__ uint32_t fmix32(uint32_t x) {
   x ^= x >> 16;
@@ -210,7 +228,7 @@ __device__ __forceinline__ void bucket_append(const Buckets& bk, uint32_t v) {
   if (n < (uint32_t)kCCap) bk.buckets[(int64_t)p * kCCap + n] = v;
   else bk.ovf[atomicAdd(bk.ovf_n, 1)] = v;
 }
-template <typename OffT, bool TABLE, bool BUCKET = false>
+template <typename OffT, bool TABLE, int kWalkers, bool BUCKET = false>
 __device__ __forceinline__ uint32_t walk_query(const HardNegLaunch& a, int64_t u, int tid,
                                                uint32_t* slots, uint32_t k0, uint32_t k1,
                                                const Buckets& bk = Buckets{}) {
@@ -298,11 +316,16 @@ __device__ __forceinline__ uint32_t walk_query(const HardNegLaunch& a, int64_t u
   return steps;
 }
 
-template <typename OffT, int E, bool TABLE>
-__global__ __launch_bounds__(kThreads) void hard_negative_kernel(HardNegLaunch a) {
+template <typename OffT, int E, bool TABLE, bool SHARE>
+__global__ __launch_bounds__(kThreads, SHARE ? 8 : 4) void hard_negative_kernel(HardNegLaunch a) {
   constexpr int N = kThreads * E;
-  __shared__ uint32_t keys[N + N / E];  // visits (sorted, padded), then head positions, rank keys
-  __shared__ uint32_t ids[N];           // pins in rank order (repeated pins by number p)
+  constexpr int kMulti = N / 2;  // most pins visited more than once
+  constexpr int kMultiE = E > 1 ? E / 2 : 1;
+  // The visits (sorted, padded), then head positions; then the repeated pins'
+  // rank keys (padded) in front and their ids, by number p, behind.
+  constexpr int kIds = kThreads * kMultiE + kThreads;
+  __shared__ uint32_t keys[kIds + kMulti > N + kThreads ? kIds + kMulti : N + kThreads];
+  uint32_t* const ids = keys + kIds;
   __shared__ int wave_tot[kWaves];
   const int WH = a.walks * a.hops;
   const uint32_t k0 = (uint32_t)(a.seed & 0xFFFFFFFFull);
@@ -326,7 +349,7 @@ __global__ __launch_bounds__(kThreads) void hard_negative_kernel(HardNegLaunch a
       const int slot = e * kThreads + tid;
       if (slot >= WH || !live) keys[slot] = kEmpty;
     }
-    if (live) my_steps += walk_query<OffT, TABLE>(a, u, tid, keys, k0, k1);
+    if (live) my_steps += walk_query<OffT, TABLE, SHARE ? 1 : kAloneWalkers>(a, u, tid, keys, k0, k1);
     __syncthreads();
 
     // ---- 2. sort visits by id ---------------------------------------------
@@ -335,63 +358,81 @@ __global__ __launch_bounds__(kThreads) void hard_negative_kernel(HardNegLaunch a
 
     // ---- 3. runs -> distinct pins, counts, rank positions ------------------
     // Thread t holds sorted elements [t*E, (t+1)*E); a head opens a run, a
-    // tail closes it. Heads are numbered d in order (block scan).
+    // tail closes it and carries its length, the pin's visit count. Only the
+    // elements stay in registers: each pass over them finds the runs again.
     const int first = tid * E;
     const uint32_t prev0 = first > 0 ? keys[padded<E>(first - 1)] : kEmpty;
     const uint32_t nextE = first + E < N ? keys[padded<E>(first + E)] : kEmpty;
-    uint32_t head_bits = 0, tail_bits = 0;
-    int nhead = 0;
+    int last_head = -1;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const uint32_t prev = e == 0 ? prev0 : k[e - 1];
-      const uint32_t next = e == E - 1 ? nextE : k[e + 1];
-      const bool head = k[e] != kEmpty && prev != k[e];
-      const bool tail = k[e] != kEmpty && next != k[e];
-      head_bits |= head ? 1u << e : 0u;
-      tail_bits |= tail ? 1u << e : 0u;
-      nhead += head ? 1 : 0;
-    }
-    int D = 0;
-    const int d0 = block_exclusive_sum(nhead, wave, lane, wave_tot, &D);  // after all reads
-    {
-      int d = d0;
+    for (int e = 0; e < E; ++e)
+      if (k[e] != kEmpty && (e == 0 ? prev0 : k[e - 1]) != k[e]) last_head = first + e;
+    // Position of the last head before this thread's elements.
+    const int head0 = block_exclusive_max(last_head, wave, lane, wave_tot);  // after all reads
+    // f(e, count) for every tail. The empty asm makes each pass compare the
+    // elements again instead of keeping 16 counts and 32 masks between passes
+    // (which spilled: a spill's reload waits behind the other workgroup's walks).
+    auto tails = [&](auto f) __attribute__((always_inline)) {
+      int head = head0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) asm volatile("" : "+v"(k[e]));
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        if (head_bits & (1u << e)) keys[d++] = (uint32_t)(first + e);  // head position of run d
+        if ((e == 0 ? prev0 : k[e - 1]) != k[e]) head = first + e;
+        if (k[e] != kEmpty && (e == E - 1 ? nextE : k[e + 1]) != k[e])
+          f(e, (uint32_t)(first + e - head + 1));
       }
-    }
-    __syncthreads();
-    // Tails: visit count of run d; repeated pins are counted for their number p.
-    // Counts are at most N <= 2^14: two per register.
-    constexpr int kPacked = (E + 1) / 2;
-    uint32_t cnt2[kPacked];
-#pragma unroll
-    for (int i = 0; i < kPacked; ++i) cnt2[i] = 0u;
-    int nmulti = 0;
+    };
+    int nmulti = 0, nsingle = 0;
+    tails([&](int, uint32_t c) __attribute__((always_inline)) {
+      nmulti += c > 1u ? 1 : 0;
+      nsingle += c == 1u ? 1 : 0;
+    });
+    int Dm = 0, Ds = 0;  // pins visited more than once, and once
+    const int p0 = block_exclusive_sum(nmulti, wave, lane, wave_tot, &Dm);
+    const int s0 = block_exclusive_sum(nsingle, wave, lane, wave_tot, &Ds);
+    const int D = Dm + Ds;
     {
-      int d = d0 - 1;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if (head_bits & (1u << e)) ++d;
-        const uint32_t c = (tail_bits & (1u << e)) ? (uint32_t)(first + e) - keys[d] + 1u : 0u;
-        cnt2[e >> 1] |= c << (16 * (e & 1));
-        nmulti += c > 1u ? 1 : 0;
-      }
-    }
-    int Dm = 0;  // pins visited more than once
-    const int p0 = block_exclusive_sum(nmulti, wave, lane, wave_tot, &Dm);  // after all reads
-    {
-      int d = d0 - 1, p = p0;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        if (head_bits & (1u << e)) ++d;
-        const uint32_t c = (cnt2[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
+      int p = p0;
+      tails([&](int e, uint32_t c) __attribute__((always_inline)) {
         if (c > 1u) {
           keys[p] = ((0xFFFFu - c) << 16) | (uint32_t)p;
           ids[p] = k[e];
           ++p;
-        } else if (c == 1u) {
-          ids[Dm + (d - p)] = k[e];  // d - p single-visit pins before this one
+        }
+      });
+    }
+
+    // Draws that fall on a pin visited once: rank Dm + s is the s-th such pin in
+    // id order, which the thread holding it writes from its registers. Each wave
+    // looks at 64 draws at a time and visits those in its own range.
+    const int64_t top = D < a.rank_hi ? (int64_t)D : (int64_t)a.rank_hi;
+    const int64_t n = top - a.rank_lo;
+    int32_t* out = a.out + qi * (int64_t)a.k;
+    auto rank_of = [&](int j) __attribute__((always_inline)) {
+      const uint4 r = philox4x32_10(make_uint4((uint32_t)u, (uint32_t)j, 0u, 1u), k0, k1);
+      return a.rank_lo + (int)(((uint64_t)r.x * (uint64_t)n) >> 32);
+    };
+    if (n > 0) {
+      const int s1 = s0 + nsingle;  // this thread's pins visited once: [s0, s1)
+      const int w0 = __builtin_amdgcn_readfirstlane(s0);
+      const int w1 = __builtin_amdgcn_readlane(s1, kWave - 1);
+      for (int j0 = 0; j0 < a.k; j0 += kWave) {
+        int want = -1;
+        if (j0 + lane < a.k) want = rank_of(j0 + lane) - Dm;
+        uint64_t mine = __ballot(want >= w0 && want < w1);
+        while (mine) {
+          const int l = __builtin_ctzll(mine);
+          mine &= mine - 1;
+          const int target = __builtin_amdgcn_readlane(want, l);
+          if (target < s0 || target >= s1) continue;
+          int s = s0;
+          tails([&](int e, uint32_t c) __attribute__((always_inline)) {
+            if (c == 1u) {
+              if (s == target) out[j0 + l] = (int32_t)k[e];
+              ++s;
+            }
+          });
         }
       }
     }
@@ -405,22 +446,16 @@ __global__ __launch_bounds__(kThreads) void hard_negative_kernel(HardNegLaunch a
 
     // ---- 4. rank order of the repeated pins: count desc, then id asc -------
     int lg_sort = 0;
-    if (Dm > 0) lg_sort = block_sort_upto<E>(keys, Dm, wave, lane);
+    if (Dm > 0) lg_sort = block_sort_upto<kMultiE>(keys, Dm, wave, lane);
 
-    // ---- 5. draws from the window -----------------------------------------
-    const int64_t top = D < a.rank_hi ? (int64_t)D : (int64_t)a.rank_hi;
-    const int64_t n = top - a.rank_lo;
-    int32_t* out = a.out + qi * (int64_t)a.k;
+    // ---- 5. draws from the window that fall on a repeated pin ---------------
     for (int j = tid; j < a.k; j += kThreads) {
-      int32_t v = -1;
-      if (n > 0) {
-        const uint4 r = philox4x32_10(make_uint4((uint32_t)u, (uint32_t)j, 0u, 1u), k0, k1);
-        const int rank = a.rank_lo + (int)(((uint64_t)r.x * (uint64_t)n) >> 32);
-        const uint32_t slot =
-            rank < Dm ? (keys[rank + (rank >> lg_sort)] & 0xFFFFu) : (uint32_t)rank;
-        v = (int32_t)ids[slot];
+      if (n <= 0) {
+        out[j] = -1;
+        continue;
       }
-      out[j] = v;
+      const int rank = rank_of(j);
+      if (rank < Dm) out[j] = (int32_t)ids[keys[rank + (rank >> lg_sort)] & 0xFFFFu];
     }
     __syncthreads();  // keys / ids are rewritten for the next query
   }
@@ -663,7 +698,7 @@ __global__ __launch_bounds__(kThreads) void hard_negative_global_kernel(HardNegL
     if (live) {
       const Buckets bk{hist, parts, buckets, ovf, &sh_i32[7]};
       // (The walkers' slots are never written in this mode.)
-      my_steps += walk_query<OffT, TABLE, true>(a, u, tid, ovf, k0, k1, bk);
+      my_steps += walk_query<OffT, TABLE, 2, true>(a, u, tid, ovf, k0, k1, bk);
     }
     __syncthreads();
     // The buckets were written through L2 by other waves: drop this CU's
@@ -903,19 +938,28 @@ __global__ __launch_bounds__(kThreads) void hard_negative_global_kernel(HardNegL
   }
 }
 
-template <typename OffT, bool TABLE>
-hipError_t launch_for_offsets(const HardNegLaunch& a, hipStream_t s) {
+template <typename OffT, bool TABLE, bool SHARE>
+hipError_t launch_on_chip(const HardNegLaunch& a, hipStream_t s) {
   const int wh = a.walks * a.hops;
   const int64_t cap = 1ll << 13;
   const dim3 grid((unsigned)(a.num_queries < cap ? a.num_queries : cap));
   const dim3 block(kThreads);
-  if (wh <= 1 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 1, TABLE>), grid, block, 0, s, a);
-  else if (wh <= 2 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 2, TABLE>), grid, block, 0, s, a);
-  else if (wh <= 4 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 4, TABLE>), grid, block, 0, s, a);
-  else if (wh <= 8 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 8, TABLE>), grid, block, 0, s, a);
-  else if (wh <= 16 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 16, TABLE>), grid, block, 0, s, a);
+  if (wh <= 1 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 1, TABLE, SHARE>), grid, block, 0, s, a);
+  else if (wh <= 2 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 2, TABLE, SHARE>), grid, block, 0, s, a);
+  else if (wh <= 4 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 4, TABLE, SHARE>), grid, block, 0, s, a);
+  else if (wh <= 8 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 8, TABLE, SHARE>), grid, block, 0, s, a);
+  else if (wh <= 16 * kThreads) hipLaunchKernelGGL((hard_negative_kernel<OffT, 16, TABLE, SHARE>), grid, block, 0, s, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+// More queries than CUs share them, two workgroups each, one walk per thread;
+// fewer have a CU each, where two walks per thread halve the walks' latency (64
+// queries of 4,096 x 4: 109 us with two or four, 110 before; 300: 271, 288 before).
+template <typename OffT, bool TABLE>
+hipError_t launch_for_offsets(const HardNegLaunch& a, hipStream_t s) {
+  return a.num_queries > 256 ? launch_on_chip<OffT, TABLE, true>(a, s)
+                             : launch_on_chip<OffT, TABLE, false>(a, s);
 }
 
 template <typename OffT, bool TABLE>
