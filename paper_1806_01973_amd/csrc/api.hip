@@ -225,14 +225,16 @@ int check_nbr(const pinsage_neighborhoods_t* n, int64_t rows, const char* what) 
 //   DENSE_THEN_POOL, bf16, d_in = d_out = 256: + W_s as product fragments for
 //                    the fused pool and W kernel (used when top_t <= 64; the
 //                    pooled chunk then stays unused).
+//   When `pre` and the pool may take column slabs: + its choice (one int).
 //   fp32, when `pre`: + Q's, W_n's and W's (or W_s's) splits, Q's and W_n's
 //                    twice (one per stream of the overlapped schedule).
 struct LayerWs {
   size_t table = 0, pchunk = 0, pooled = 0, wsp = 0;
-  size_t qs = 0, wns = 0, wss = 0;
+  size_t qs = 0, wns = 0, wss = 0, choice = 0;
   bool chained = false;
   size_t base() const { return table + pchunk + pooled + wsp; }
-  size_t total() const { return base() + 2 * (qs + wns) + wss; }
+  size_t choice_at() const { return base() + 2 * (qs + wns) + wss; }
+  size_t total() const { return choice_at() + choice; }
 };
 
 bool chained_layer(const pinsage_layer_t* L) {
@@ -262,6 +264,8 @@ LayerWs layer_ws(const pinsage_layer_t* L, int64_t n_transform, int64_t n_out, b
     w.qs = split_ws(L->dtype, n_transform, L->m, L->d_in);
     if (split) w.wns = split_ws(L->dtype, n_transform, L->d_out, L->m);
     w.wss = split_ws(L->dtype, n_out, L->d_out, split ? L->d_in : L->d_in + L->m);
+    if (!w.wsp && pool_slabs_wanted(n_transform, (int64_t)(split ? L->d_out : L->m) * es, n_out))
+      w.choice = kAlign;
   }
   return w;
 }
@@ -389,7 +393,7 @@ int run_transform(const pinsage_layer_t* L, const void* h_in, int64_t n_in, int6
 int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
                    int64_t n_transform, const pinsage_neighborhoods_t* nbr,
                    const int32_t* self_rows, void* h_out, int64_t n_out, void* ws, bool pre,
-                   hipStream_t s) {
+                   hipStream_t s, bool short_rows = false) {
   const bool bf16 = L->dtype == PINSAGE_BF16;
   const bool split = L->dataflow == PINSAGE_DENSE_THEN_POOL;
   const size_t es = elem_size(L->dtype);
@@ -439,6 +443,7 @@ int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
     pl.rows = rows;
     pl.out = nbuf;
     pl.mode = (int)L->pool;
+    if (lw.choice && !short_rows) pl.slabbed = reinterpret_cast<int*>(table + lw.choice_at());
     e = launch_pool(pl, s);
     if (e != hipSuccess) return hip_fail(e, "pool launch");
 
@@ -482,10 +487,11 @@ int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
 int run_layer(const pinsage_layer_t* L, const void* h_in, int64_t n_in, int64_t n_transform,
               const int32_t* transform_rows, const pinsage_neighborhoods_t* nbr,
               const int32_t* self_rows, void* h_out, int64_t n_out, void* ws, bool pre,
-              hipStream_t s) {
+              hipStream_t s, bool short_rows = false) {
   int st = run_transform(L, h_in, n_in, n_transform, transform_rows, n_out, ws, pre, s);
   if (st) return st;
-  return run_pool_dense(L, h_in, n_in, n_transform, nbr, self_rows, h_out, n_out, ws, pre, s);
+  return run_pool_dense(L, h_in, n_in, n_transform, nbr, self_rows, h_out, n_out, ws, pre, s,
+                        short_rows);
 }
 
 // ---- walks beside the first layer's transform (embed_all) -----------------
@@ -970,9 +976,10 @@ int pinsage_embed_all_bipartite(const pinsage_graph_t* graph, uint64_t seed,
     void* dst = (k == num_layers - 1) ? h_out : hbuf[k % 2];
     if (k == 0)
       st = run_layer(&layers[k], cur, graph->num_pins, n, pin_map, nbr_out, pin_map, dst, n, ws,
-                     pre, s);
+                     pre, s, true);
     else
-      st = run_layer(&layers[k], cur, n, n, nullptr, nbr_out, nullptr, dst, n, ws, pre, s);
+      st = run_layer(&layers[k], cur, n, n, nullptr, nbr_out, nullptr, dst, n, ws, pre, s,
+                     true);
     if (st) return st;
     cur = dst;
   }

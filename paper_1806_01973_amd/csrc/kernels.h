@@ -126,7 +126,11 @@ struct PoolLaunch {
   int64_t rows;
   void* out;
   int mode;  // PoolMode
+  // Device int for the launch's choice between whole rows and column slabs, or
+  // null (whole rows); give one when pool_slabs_wanted and the rows may be deep.
+  int* slabbed = nullptr;
 };
+bool pool_slabs_wanted(int64_t n_transform, int64_t row_bytes, int64_t rows);
 hipError_t launch_pool(const PoolLaunch& a, hipStream_t s);
 
 // Pool and W fused (poolw.hip): out[r] = L2norm(ReLU(W_s h[self(r)] + pool(R, N(r))

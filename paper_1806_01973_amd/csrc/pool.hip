@@ -104,6 +104,7 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolLaunch a) {
   constexpr int VN = V::kN;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
+  if (a.slabbed && *a.slabbed) return;  // pool_slab_kernel has pooled the rows
   const int m = a.m;
   const int T = a.T;
   const Raw* __restrict__ P = static_cast<const Raw*>(a.P);
@@ -352,16 +353,245 @@ __global__ __launch_bounds__(256) void pool_head_kernel(PoolLaunch a) {
   }
 }
 
+// Decides between whole rows and column slabs (below) from kProbes sampled slots:
+// slabs pay when the neighbourhoods are deep (a header is read per slab) and when
+// some rows are gathered far more often than others, so that the slices of the
+// popular ones stay in the L2s. The sample's pairs of equal ids estimate the sum
+// of squared gather frequencies; 12 pairs among 2,048 samples is 6e-6, as when the
+// 32K rows whose 128-byte slices fill one XCD's L2 take 44% of the gathers.
+constexpr int kProbes = 2048;
+__global__ __launch_bounds__(1024) void pool_probe_kernel(PoolLaunch a, int min_live) {
+  constexpr int kSlots = 2 * kProbes;
+  __shared__ uint32_t keys[kSlots], seen[kSlots];
+  __shared__ int live, pairs;
+  for (int i = threadIdx.x; i < kSlots; i += 1024) {
+    keys[i] = 0xFFFFFFFFu;
+    seen[i] = 0u;
+  }
+  if (threadIdx.x == 0) live = pairs = 0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < kProbes; i += 1024) {
+    const uint32_t x = (uint32_t)i * 0x9E3779B9u;
+    const int64_t row = (int64_t)(((uint64_t)x * (uint64_t)a.rows) >> 32);
+    const int t = (int)(((uint64_t)(x * 0x85EBCA6Bu) * (uint64_t)a.T) >> 32);
+    const int32_t v = a.idx[row * a.T + t];
+    if ((uint64_t)(int64_t)v >= (uint64_t)a.n_transform) continue;
+    atomicAdd(&live, 1);
+    uint32_t h = ((uint32_t)v * 0x9E3779B9u) >> (32 - 12);
+    static_assert(kSlots == 1 << 12, "home slot");
+    for (;;) {  // half full at most, so a free slot is found
+      const uint32_t k = atomicCAS(&keys[h], 0xFFFFFFFFu, (uint32_t)v);
+      if (k == 0xFFFFFFFFu || k == (uint32_t)v) break;
+      h = (h + 1) & (kSlots - 1);
+    }
+    atomicAdd(&pairs, (int)atomicAdd(&seen[h], 1u));
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int64_t n = live;
+    *a.slabbed = n * a.T >= (int64_t)min_live * kProbes &&
+                 (int64_t)pairs * kProbes * kProbes >= 12 * n * n;
+  }
+}
+
+// Tables of wide rows beyond the L2s: the pool runs over column slabs of GL
+// 16-byte vectors, all rows of one slab before the next (blocks are dispatched in
+// order), so that an L2 holds the slices of 8 or 4 times as many popular rows as
+// it holds whole rows, and the last-level cache a slab of the whole table. An item
+// is one row of one slab: RG = 64 / GL lane groups gather its slots, every slot in
+// flight at once, each group summing slots g, g + RG, ... in rank order. A narrow
+// item costs issue slots as much as bytes, so: the next row's header is loaded
+// under the current row's gathers; a slot's byte offset and weight pass through
+// LDS (two lane permutes and a 64-bit multiply per slot otherwise); and the groups
+// are added by halving (each step exchanges half of the values a lane still
+// holds), in the same tree as a butterfly. pool_probe_kernel decides; this kernel
+// and pool_kernel (whole rows, launched behind it) each end at once if not chosen
+// (with the probe about 20 us where whole rows are).
+// What bounds it: cache bandwidth, about 13 TB/s of gathered bytes, and at 128
+// bytes an item the issue slots. T = 50, pin degree Zipf(2): 1M rows of 1 KB
+// (fp32) 6.60 -> 5.19 ms; 300K of 1 KB (bf16) 1.72 -> 1.36; 100K of 2 KB, max
+// 1.09 -> 0.82. Where popularity is uniform, 800K rows of 1 KB took 6.67 ms whole
+// and 7.03 in slabs; with 10 neighbours a row 1.06 and 1.51 (whence the probe).
+constexpr int kSlabBlockRows = 32 * kWavesPerBlock;  // 64 per wave: 3-5% slower
+template <bool BF16, int MODE, int GL>
+__global__ __launch_bounds__(256, GL == 8 ? 7 : 4) void pool_slab_kernel(PoolLaunch a) {
+  using V = Vec<BF16>;
+  using Raw = typename V::Raw;
+  constexpr int VN = V::kN;
+  constexpr int RG = kWave / GL;
+  constexpr int NB = kWave / RG;  // slots per lane group: T <= 64 in one batch
+  constexpr int ESZ = BF16 ? 2 : 4;
+  __shared__ uint2 slots_all[kWavesPerBlock][kWave];  // byte offset, weight per slot
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (!*a.slabbed) return;
+  uint2* const slots = slots_all[wave];
+  const int T = a.T;
+  const int grp = lane / GL, c = lane % GL;
+  const uint32_t row_bytes = (uint32_t)a.m * ESZ;
+  // Block b: slab b / blocks per slab, kSlabBlockRows of its rows.
+  const uint32_t per_slab = (uint32_t)((a.rows + kSlabBlockRows - 1) / kSlabBlockRows);
+  const uint32_t slab = blockIdx.x / per_slab;
+  const uint32_t col = slab * GL * 16 + c * 16;  // byte of the row
+  const bool col_ok = col < row_bytes;
+  const unsigned char* const P = static_cast<const unsigned char*>(a.P);
+  struct Head {
+    int32_t v = -1;
+    float w = 0.0f;
+    int cnt = 0;
+  };
+  auto load_head = [&](int64_t row) __attribute__((always_inline)) {
+    Head h;
+    if (lane < T) {
+      h.v = a.idx[row * T + lane];
+      if constexpr (MODE == kPoolImportance) {
+        if (a.weights) h.w = a.weights[row * T + lane];
+        else h.cnt = a.counts[row * T + lane];
+      }
+    }
+    return h;
+  };
+
+  int64_t row = (int64_t)(blockIdx.x % per_slab) * kSlabBlockRows;
+  const int64_t end = row + kSlabBlockRows < a.rows ? row + kSlabBlockRows : a.rows;
+  row += wave;
+  Head head;
+  if (row < end) head = load_head(row);
+  for (; row < end; row += kWavesPerBlock) {
+    const Head cur = head;
+    if (row + kWavesPerBlock < end) head = load_head(row + kWavesPerBlock);
+
+    const bool valid = (uint64_t)(int64_t)cur.v < (uint64_t)a.n_transform;
+    float alpha = 0.0f;
+    if constexpr (MODE == kPoolMean) {
+      const int total = wave_sum_i32(valid ? 1 : 0);
+      alpha = valid ? 1.0f / (float)total : 0.0f;
+    } else if constexpr (MODE == kPoolImportance) {
+      if (a.weights) {
+        alpha = valid ? cur.w : 0.0f;
+      } else {
+        const int total = wave_sum_i32(cur.cnt);  // every slot, as the walk kernel's S
+        alpha = valid ? (float)cur.cnt / (float)total : 0.0f;
+      }
+    }
+    slots[lane] = make_uint2(valid ? (uint32_t)cur.v * row_bytes : 0xFFFFFFFFu,
+                             __float_as_uint(alpha));
+    wave_lds_sync();
+    Raw buf[NB];
+    bool ok[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const uint32_t at = slots[i * RG + grp].x;
+      ok[i] = at != 0xFFFFFFFFu && col_ok;
+      buf[i] = ok[i] ? *reinterpret_cast<const Raw*>(P + (at + col)) : Raw{};
+    }
+    float acc[VN];
+#pragma unroll
+    for (int k = 0; k < VN; ++k) acc[k] = MODE == kPoolMax ? -INFINITY : 0.0f;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      float f[VN];
+      V::to_f32(buf[i], f);
+      const float al = MODE == kPoolMax ? 0.0f : __uint_as_float(slots[i * RG + grp].y);
+#pragma unroll
+      for (int k = 0; k < VN; ++k) {
+        // Absent slots: weight 0 and zeros; for the max they take no part.
+        if constexpr (MODE == kPoolMax) acc[k] = ok[i] ? fmaxf(acc[k], f[k]) : acc[k];
+        else acc[k] = fmaf(al, f[k], acc[k]);
+      }
+    }
+    wave_lds_sync();  // the slots are rewritten for the next row
+    // Sum (or max) over the groups; the lane ends with elements [e0, e0 + left)
+    // of its vector, the same in `copies` lanes.
+    int left = VN, e0 = 0;
+    bool first = true;
+#pragma unroll
+    for (int o = kWave / 2; o >= GL; o >>= 1) {
+      const bool up = (lane & o) != 0;
+      if (left > 1) {
+        left /= 2;
+#pragma unroll
+        for (int k = 0; k < VN / 2; ++k) {
+          if (k >= left) continue;
+          const float give = up ? acc[k] : acc[k + left];
+          const float keep = up ? acc[k + left] : acc[k];
+          const float got = __shfl_xor(give, o);
+          acc[k] = MODE == kPoolMax ? fmaxf(keep, got) : keep + got;
+        }
+        e0 += up ? left : 0;
+      } else {
+        const float got = __shfl_xor(acc[0], o);
+        acc[0] = MODE == kPoolMax ? fmaxf(acc[0], got) : acc[0] + got;
+        first = first && !up;
+      }
+    }
+    if constexpr (MODE == kPoolMax) {
+      const bool row_any = __ballot(valid) != 0ull;
+#pragma unroll
+      for (int k = 0; k < VN; ++k) acc[k] = row_any ? acc[k] : 0.0f;
+    }
+    constexpr int LEFT = VN > RG ? VN / RG : 1;
+    if (first && col_ok) {
+      unsigned char* const o =
+          static_cast<unsigned char*>(a.out) + row * (int64_t)row_bytes + col + e0 * ESZ;
+      if constexpr (!BF16) {
+        *reinterpret_cast<float*>(o) = acc[0];
+      } else if constexpr (LEFT == 2) {
+        *reinterpret_cast<uint32_t*>(o) =
+            (uint32_t)f32_to_bf16(acc[0]) | ((uint32_t)f32_to_bf16(acc[1]) << 16);
+      } else {
+        *reinterpret_cast<uint16_t*>(o) = f32_to_bf16(acc[0]);
+      }
+      static_assert(BF16 ? LEFT <= 2 : LEFT == 1, "elements left per lane");
+    }
+  }
+}
+
+// Fewest live slots per row (on average) that pay for a header per slab: at 27 of
+// T = 27, fp32 rows gained (396 -> 352 us, 150K of 1 KB) and bf16 rows lost (891 ->
+// 1166, 300K of 1 KB: twice the values per lane to add over the groups).
+inline int min_live(bool bf16) { return bf16 ? 40 : 22; }
+
+// Bytes of a row per slab, 0 for whole rows. 256 while a slab takes at most half
+// of the last-level cache (256 MB), 128 up to all of it. Measured, whole / 256 / 128
+// (us): 20K rows of 2 KB 146 / 153 / 149; 50K of 1 KB 218 / 182 / 187; 150K of 1 KB
+// 724 / 542 / 553; 300K of 1 KB in bf16 1722 / 1336 / 1611; 700K of 1 KB 4427 / 3683
+// / 3384; 1.6M 10855 / 9812 / 9641; 2M in bf16 14339 / 13441 / 13073.
+inline int slab_bytes(const PoolLaunch& a) {
+  if (!a.slabbed || a.T > kWave || a.T < min_live(a.bf16)) return 0;
+  if (a.n_transform * 256 <= (128ll << 20)) return 256;
+  return a.n_transform * 128 <= (256ll << 20) ? 128 : 0;
+}
+
+template <bool BF16, int MODE>
+hipError_t launch_slabs(const PoolLaunch& a, int bytes, hipStream_t s) {
+  const int64_t slabs = ((int64_t)a.m * (BF16 ? 2 : 4) + bytes - 1) / bytes;
+  const int64_t blocks = slabs * ((a.rows + kSlabBlockRows - 1) / kSlabBlockRows);
+  if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(256);
+  hipLaunchKernelGGL(pool_probe_kernel, dim3(1), dim3(1024), 0, s, a, min_live(BF16));
+  if (bytes == 256) hipLaunchKernelGGL((pool_slab_kernel<BF16, MODE, 16>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((pool_slab_kernel<BF16, MODE, 8>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
 template <bool BF16, int MODE>
 hipError_t launch_batched(const PoolLaunch& a, dim3 grid, dim3 block, int slabs, int vec_per_row,
                           hipStream_t s);
 
 template <bool BF16, int MODE>
-hipError_t launch_mode(const PoolLaunch& a, hipStream_t s) {
+hipError_t launch_mode(PoolLaunch a, hipStream_t s) {
   constexpr int VN = BF16 ? 8 : 4;
   const int slabs = (a.m / VN + kWave - 1) / kWave;
   const int64_t blocks_needed = (a.rows + kWavesPerBlock - 1) / kWavesPerBlock;
-  const int64_t cap = 1ll << 22;
+  int64_t cap = 1ll << 22;
+  if (const int bytes = slab_bytes(a)) {
+    const hipError_t e = launch_slabs<BF16, MODE>(a, bytes, s);
+    if (e != hipSuccess) return e;
+    cap = 1ll << 15;  // whole rows behind it, in fewer blocks to end
+  } else {
+    a.slabbed = nullptr;
+  }
   const dim3 grid((unsigned)(blocks_needed < cap ? blocks_needed : cap));
   const dim3 block(256);
   const int vec_per_row = a.m / VN;
@@ -410,6 +640,13 @@ hipError_t launch_typed(const PoolLaunch& a, hipStream_t s) {
 }
 
 }  // namespace
+
+// Tables the slabs are for: rows of 1 KB and more, 48 MB and more (byte offsets
+// are 32 bits), enough rows for the probe's launch not to matter.
+bool pool_slabs_wanted(int64_t n_transform, int64_t row_bytes, int64_t rows) {
+  const int64_t table = n_transform * row_bytes;
+  return row_bytes >= 1024 && rows >= 16384 && table >= (48ll << 20) && table < (1ll << 32) - 16;
+}
 
 hipError_t launch_pool(const PoolLaunch& a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
