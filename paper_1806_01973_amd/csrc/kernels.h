@@ -153,11 +153,12 @@ struct PoolWLaunch {
   const float* bias;       // [256]
   void* out;               // [rows][256]
   int64_t rows;
+  int group = 32;          // rows per wave and turn (set by the launch)
 };
 bool pool_w_supported(int d_in, int d_out, bool bf16, int T);
 size_t pool_w_ws_bytes();
 hipError_t launch_permute_ws(const void* W, int64_t ldw, void* Wsp, hipStream_t s);
-hipError_t launch_pool_w(const PoolWLaunch& a, hipStream_t s);
+hipError_t launch_pool_w(PoolWLaunch a, hipStream_t s);
 
 // C[r][c] = epilogue(sum_k A[r][k] * B[c][k] + bias[c] + addend[r][c]) where
 // the A row is the concatenation of A0[rowmap ? rowmap[r] : r][0:K0] and

@@ -54,7 +54,9 @@ __global__ void permute_ws_kernel(const uint16_t* __restrict__ W, int64_t ldw,
   }
 }
 
-template <int MODE>
+// FULL: 32 rows per wave and turn (a.group otherwise; as a variable it costs the
+// loop registers).
+template <int MODE, bool FULL>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void pool_w_kernel(PoolWLaunch a) {
   __shared__ __attribute__((aligned(16))) unsigned char strip_all[kWaves][32 * kRowB];
@@ -68,12 +70,13 @@ void pool_w_kernel(PoolWLaunch a) {
   const uint4* __restrict__ R = static_cast<const uint4*>(a.R);  // 32 vectors per row
   const int grp = lane >> 5, c = lane & 31;                       // pool: lane groups
   const int h = lane >> 5, r32 = lane & 31;                       // product: row, half
-  const int64_t groups = (a.rows + 31) / 32;
+  const int group = FULL ? 32 : a.group;
+  const int64_t groups = (a.rows + group - 1) / group;
 
   for (int64_t g32 = (int64_t)blockIdx.x * kWaves + wave; g32 < groups;
        g32 += (int64_t)gridDim.x * kWaves) {
-    const int64_t rbase = g32 * 32;
-    const int nrows = a.rows - rbase < 32 ? (int)(a.rows - rbase) : 32;
+    const int64_t rbase = g32 * group;
+    const int nrows = a.rows - rbase < group ? (int)(a.rows - rbase) : group;
 
     // ---- 1. pool the group's rows into the strip ---------------------------
     for (int i = 0; i < nrows; ++i) {
@@ -246,6 +249,13 @@ void pool_w_kernel(PoolWLaunch a) {
   }
 }
 
+template <int MODE>
+void launch_pool_w_mode(const PoolWLaunch& a, dim3 grid, hipStream_t s) {
+  const dim3 block(64 * kWaves);
+  if (a.group == 32) hipLaunchKernelGGL((pool_w_kernel<MODE, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((pool_w_kernel<MODE, false>), grid, block, 0, s, a);
+}
+
 }  // namespace
 
 bool pool_w_supported(int d_in, int d_out, bool bf16, int T) {
@@ -260,26 +270,26 @@ hipError_t launch_permute_ws(const void* W, int64_t ldw, void* Wsp, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_pool_w(const PoolWLaunch& a, hipStream_t s) {
+hipError_t launch_pool_w(PoolWLaunch a, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   if (a.T < 1 || a.T > 64) return hipErrorInvalidValue;
   ProfileScope prof(kKPoolW, s);
-  const int64_t groups = (a.rows + 31) / 32;
+  // Rows per wave and turn: 32, or the fewest that fill the chip's wave slots (2
+  // per SIMD) for the same number of turns, so that the last turn is not nearly
+  // empty: 99K rows are 1.5 turns of 32 (382 us) but two of 25 (365), 4.5K rows
+  // 7% of a turn of 32 (147 us) but one of 3 (55). Beyond 8 turns the last
+  // one hardly counts, and a full product serves more rows.
+  const int64_t slots = 256 * 2 * kWaves, turns = (a.rows + 32 * slots - 1) / (32 * slots);
+  a.group = turns > 8 ? 32 : (int)((a.rows + turns * slots - 1) / (turns * slots));
+  const int64_t groups = (a.rows + a.group - 1) / a.group;
   const int64_t blocks_needed = (groups + kWaves - 1) / kWaves;
   const int64_t cap = 1ll << 20;
   const dim3 grid((unsigned)(blocks_needed < cap ? blocks_needed : cap));
   switch (a.mode) {
-    case kPoolImportance:
-      hipLaunchKernelGGL(pool_w_kernel<kPoolImportance>, grid, dim3(64 * kWaves), 0, s, a);
-      break;
-    case kPoolMean:
-      hipLaunchKernelGGL(pool_w_kernel<kPoolMean>, grid, dim3(64 * kWaves), 0, s, a);
-      break;
-    case kPoolMax:
-      hipLaunchKernelGGL(pool_w_kernel<kPoolMax>, grid, dim3(64 * kWaves), 0, s, a);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case kPoolImportance: launch_pool_w_mode<kPoolImportance>(a, grid, s); break;
+    case kPoolMean: launch_pool_w_mode<kPoolMean>(a, grid, s); break;
+    case kPoolMax: launch_pool_w_mode<kPoolMax>(a, grid, s); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
