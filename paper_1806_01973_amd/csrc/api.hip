@@ -1595,9 +1595,8 @@ int pinsage_minibatch_forward(const pinsage_graph_t* graph, const pinsage_walk_p
   };
   // Sorted unique set of level k from the flags, its size and pin count.
   auto scan_level = [&](int k) -> int {
-    PINSAGE_TRY(launch_flag_scan(flags, N, tiles, pos, set_of(k), p.U[k], ctr, s), "frontier scan");
-    PINSAGE_TRY(launch_count_below(set_of(k), ctr, p.U[k], graph->num_pins, ctr + 1, s),
-                "pin count");
+    PINSAGE_TRY(launch_flag_scan(flags, N, tiles, pos, set_of(k), p.U[k], graph->num_pins, ctr, s),
+                "frontier scan");
     int r = read_counters(ctr, host, 2, s);
     if (r) return r;
     size[k] = host[0];
@@ -1611,25 +1610,21 @@ int pinsage_minibatch_forward(const pinsage_graph_t* graph, const pinsage_walk_p
   if (total_steps) PINSAGE_TRY(launch_zero_u64(total_steps, 1, s), "step counter reset");
   // Level K: the targets of the minibatch (Algorithm 2, S^(K) = M).
   PINSAGE_TRY(launch_fill_zero_u8(flags, N, s), "flag reset");
-  PINSAGE_TRY(launch_mark(pairs->queries, B, N, flags, s), "mark");
-  PINSAGE_TRY(launch_mark(pairs->positives, B, N, flags, s), "mark");
-  PINSAGE_TRY(launch_mark(pairs->negatives, n_neg, N, flags, s), "mark");
-  PINSAGE_TRY(launch_mark(pairs->hard_negatives, B * n_hard, N, flags, s), "mark");
+  const IdLists targets{{pairs->queries, pairs->positives, pairs->negatives, pairs->hard_negatives},
+                        {B, B, n_neg, B * n_hard}};
+  PINSAGE_TRY(launch_mark(targets, N, flags, s), "mark");
   if ((st = scan_level(K))) return st;
-  PINSAGE_TRY(launch_remap(pairs->queries, B, N, pos, rows, s), "remap");
-  PINSAGE_TRY(launch_remap(pairs->positives, B, N, pos, rows + B, s), "remap");
-  PINSAGE_TRY(launch_remap(pairs->negatives, n_neg, N, pos, rows + 2 * B, s), "remap");
-  PINSAGE_TRY(launch_remap(pairs->hard_negatives, B * n_hard, N, pos, rows + 2 * B + n_neg, s),
-              "remap");
+  PINSAGE_TRY(launch_remap(targets, N, pos, rows, s), "remap");
   if ((st = walk_level(K))) return st;
   // Levels K-1 .. 0: S^(k) = S^(k+1) u N(S^(k+1)); re-index level k+1.
   for (int k = K - 1; k >= 0; --k) {
-    PINSAGE_TRY(launch_fill_zero_u8(flags, N, s), "flag reset");
-    PINSAGE_TRY(launch_mark(set_of(k + 1), size[k + 1], N, flags, s), "mark");
-    PINSAGE_TRY(launch_mark(nidx_of(k + 1), size[k + 1] * T, N, flags, s), "mark");
+    // (The scan of level k + 1 left the flags zero.)
+    const IdLists level{{set_of(k + 1), nidx_of(k + 1)}, {size[k + 1], size[k + 1] * T}};
+    PINSAGE_TRY(launch_mark(level, N, flags, s), "mark");
     if ((st = scan_level(k))) return st;
-    PINSAGE_TRY(launch_remap(nidx_of(k + 1), size[k + 1] * T, N, pos, nidx_of(k + 1), s), "remap");
-    PINSAGE_TRY(launch_remap(set_of(k + 1), size[k + 1], N, pos, self_of(k + 1), s), "remap");
+    const IdLists nbrs{{nidx_of(k + 1)}, {size[k + 1] * T}}, self{{set_of(k + 1)}, {size[k + 1]}};
+    PINSAGE_TRY(launch_remap(nbrs, N, pos, nidx_of(k + 1), s), "remap");
+    PINSAGE_TRY(launch_remap(self, N, pos, self_of(k + 1), s), "remap");
     if (k >= 1 && (st = walk_level(k))) return st;
   }
 

@@ -259,17 +259,23 @@ hipError_t launch_loss(const LossLaunch& a, hipStream_t s);
 
 // Frontier machinery of the minibatch forward (node flags + exclusive scan).
 hipError_t launch_fill_zero_u8(uint8_t* p, int64_t n, hipStream_t s);
-hipError_t launch_mark(const int32_t* ids, int64_t n, int64_t N, uint8_t* flags, hipStream_t s);
+// Up to four id lists taken one after another by one launch (each small launch
+// costs about 5 us of the stream: a training minibatch's frontiers took 33).
+struct IdLists {
+  const int32_t* ids[4] = {};
+  int64_t n[4] = {};
+};
+hipError_t launch_mark(const IdLists& ids, int64_t N, uint8_t* flags, hipStream_t s);
 int64_t scan_tiles(int64_t N);
 // set[0..total) = sorted flagged ids (entries past cap are dropped), pos[id] =
-// index of id in set (flagged ids only).
-hipError_t launch_flag_scan(const uint8_t* flags, int64_t N, int32_t* tile_sums, int32_t* pos,
-                            int32_t* set, int64_t cap, long long* total, hipStream_t s);
-// *count = entries of the sorted set (length *size_dev <= cap) below bound.
-hipError_t launch_count_below(const int32_t* set, const long long* size_dev, int64_t cap,
-                              int64_t bound, long long* count, hipStream_t s);
-// out[i] = pos[in[i]] for in[i] in [0, N), else -1 (in-place allowed).
-hipError_t launch_remap(const int32_t* in, int64_t n, int64_t N, const int32_t* pos, int32_t* out,
+// index of id in set (flagged ids only), counts[0] = total, counts[1] = flagged
+// ids below bound; the flags (16-byte aligned) end as zeros.
+hipError_t launch_flag_scan(uint8_t* flags, int64_t N, int32_t* tile_sums, int32_t* pos,
+                            int32_t* set, int64_t cap, int64_t bound, long long* counts,
+                            hipStream_t s);
+// out[i] = pos[v] for element i, v, of the lists when v lies in [0, N), else -1
+// (in place with a single list).
+hipError_t launch_remap(const IdLists& in, int64_t N, const int32_t* pos, int32_t* out,
                         hipStream_t s);
 hipError_t launch_gather_rows(const void* table, const int32_t* rows, int64_t n, int64_t row_bytes,
                               void* out, hipStream_t s);

@@ -25,11 +25,36 @@ __global__ void fill_u8_kernel(uint8_t* p, int64_t n) {
     p[i] = 0;
 }
 
-__global__ void mark_kernel(const int32_t* ids, int64_t n, int64_t N, uint8_t* flags) {
+// Element i of up to four id lists one after another.
+__device__ __forceinline__ int32_t list_at(const IdLists& l, int64_t i) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if (i < l.n[k]) return l.ids[k][i];
+    i -= l.n[k];
+  }
+  return l.ids[3][i];
+}
+
+__global__ void mark_kernel(IdLists ids, int64_t n, int64_t N, uint8_t* flags) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t v = ids[i];
+    const int32_t v = list_at(ids, i);
     if (v >= 0 && (int64_t)v < N) flags[v] = 1;
+  }
+}
+
+// A thread's kScanPerThread flags (0 past N), 16 bytes in one load where all exist.
+__device__ __forceinline__ void load_flags(const uint8_t* flags, int64_t base, int64_t N,
+                                           uint8_t (&f)[kScanPerThread]) {
+  static_assert(kScanPerThread == 16, "one 16-byte load");
+  if (base + kScanPerThread <= N) {
+    const uint4 v = *reinterpret_cast<const uint4*>(flags + base);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < kScanPerThread; ++e) f[e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
+  } else {
+#pragma unroll
+    for (int e = 0; e < kScanPerThread; ++e) f[e] = base + e < N ? flags[base + e] : 0;
   }
 }
 
@@ -57,17 +82,20 @@ __global__ __launch_bounds__(kScanThreads) void scan_tile_sums_kernel(const uint
                                                                       int64_t N, int32_t* sums) {
   __shared__ int lds[65];
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPerThread;
+  uint8_t f[kScanPerThread];
+  load_flags(flags, base, N, f);
   int s = 0;
 #pragma unroll
-  for (int e = 0; e < kScanPerThread; ++e)
-    if (base + e < N) s += flags[base + e];
+  for (int e = 0; e < kScanPerThread; ++e) s += f[e];
   int total = 0;
   block_exclusive_scan(s, lds, &total);
   if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
+// counts[0] = flagged ids, and with all_below counts[1] as well.
 __global__ __launch_bounds__(1024) void scan_tile_offsets_kernel(int32_t* sums, int64_t ntiles,
-                                                                 long long* total) {
+                                                                 long long* counts,
+                                                                 bool all_below) {
   __shared__ int lds[65];
   long long carry = 0;
   for (int64_t c = 0; c < ntiles; c += blockDim.x) {
@@ -78,51 +106,42 @@ __global__ __launch_bounds__(1024) void scan_tile_offsets_kernel(int32_t* sums, 
     if (i < ntiles) sums[i] = (int32_t)(carry + ex);
     carry += chunk;
   }
-  if (threadIdx.x == 0) *total = carry;
+  if (threadIdx.x == 0) {
+    counts[0] = carry;
+    if (all_below) counts[1] = carry;
+  }
 }
 
+// set, pos; counts[1] = flagged ids below `bound` (when bound < N); the flags are
+// left zero for the next level.
 __global__ __launch_bounds__(kScanThreads) void scan_tile_finish_kernel(
-    const uint8_t* flags, int64_t N, const int32_t* offsets, int32_t* pos, int32_t* set,
-    int64_t cap) {
+    uint8_t* flags, int64_t N, const int32_t* offsets, int32_t* pos, int32_t* set, int64_t cap,
+    int64_t bound, long long* counts) {
   __shared__ int lds[65];
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPerThread;
   uint8_t f[kScanPerThread];
+  load_flags(flags, base, N, f);
   int s = 0;
 #pragma unroll
-  for (int e = 0; e < kScanPerThread; ++e) {
-    f[e] = (base + e < N) ? flags[base + e] : 0;
-    s += f[e];
-  }
+  for (int e = 0; e < kScanPerThread; ++e) s += f[e];
   int total = 0;
   int p = offsets[blockIdx.x] + block_exclusive_scan(s, lds, &total);
 #pragma unroll
   for (int e = 0; e < kScanPerThread; ++e) {
+    if (base + e == bound && base + e < N) counts[1] = p;
     if (f[e]) {
       pos[base + e] = p;
       if (p < cap) set[p] = (int32_t)(base + e);
       ++p;
+      flags[base + e] = 0;
     }
   }
 }
 
-// *count = number of entries of the sorted set below `bound` (the pins); the
-// set's length is read from device memory (at most cap).
-__global__ void count_below_kernel(const int32_t* set, const long long* size_dev, int64_t cap,
-                                   int64_t bound, long long* count) {
-  const int64_t size = *size_dev < cap ? *size_dev : cap;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < size;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const bool below = set[i] < bound;
-    const bool next_above = (i + 1 == size) || set[i + 1] >= bound;
-    if (below && next_above) *count = i + 1;
-  }
-}
-
-__global__ void remap_kernel(const int32_t* in, int64_t n, int64_t N, const int32_t* pos,
-                             int32_t* out) {
+__global__ void remap_kernel(IdLists in, int64_t n, int64_t N, const int32_t* pos, int32_t* out) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t v = in[i];
+    const int32_t v = list_at(in, i);
     out[i] = (v >= 0 && (int64_t)v < N) ? pos[v] : -1;
   }
 }
@@ -350,7 +369,10 @@ hipError_t launch_fill_zero_u8(uint8_t* p, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_mark(const int32_t* ids, int64_t n, int64_t N, uint8_t* flags, hipStream_t s) {
+static int64_t list_size(const IdLists& l) { return l.n[0] + l.n[1] + l.n[2] + l.n[3]; }
+
+hipError_t launch_mark(const IdLists& ids, int64_t N, uint8_t* flags, hipStream_t s) {
+  const int64_t n = list_size(ids);
   if (n <= 0) return hipSuccess;
   ProfileScope prof(kKMinibatch, s);
   hipLaunchKernelGGL(mark_kernel, grid_for(n), dim3(256), 0, s, ids, n, N, flags);
@@ -359,30 +381,24 @@ hipError_t launch_mark(const int32_t* ids, int64_t n, int64_t N, uint8_t* flags,
 
 int64_t scan_tiles(int64_t N) { return (N + kScanTile - 1) / kScanTile; }
 
-hipError_t launch_flag_scan(const uint8_t* flags, int64_t N, int32_t* tile_sums, int32_t* pos,
-                            int32_t* set, int64_t cap, long long* total, hipStream_t s) {
+hipError_t launch_flag_scan(uint8_t* flags, int64_t N, int32_t* tile_sums, int32_t* pos,
+                            int32_t* set, int64_t cap, int64_t bound, long long* counts,
+                            hipStream_t s) {
   const int64_t tiles = scan_tiles(N);
   if (tiles <= 0 || tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
   ProfileScope prof(kKMinibatch, s);
   hipLaunchKernelGGL(scan_tile_sums_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s,
                      flags, N, tile_sums);
-  hipLaunchKernelGGL(scan_tile_offsets_kernel, dim3(1), dim3(1024), 0, s, tile_sums, tiles, total);
+  hipLaunchKernelGGL(scan_tile_offsets_kernel, dim3(1), dim3(1024), 0, s, tile_sums, tiles, counts,
+                     bound >= N);
   hipLaunchKernelGGL(scan_tile_finish_kernel, dim3((unsigned)tiles), dim3(kScanThreads), 0, s,
-                     flags, N, tile_sums, pos, set, cap);
+                     flags, N, tile_sums, pos, set, cap, bound, counts);
   return hipGetLastError();
 }
 
-hipError_t launch_count_below(const int32_t* set, const long long* size_dev, int64_t cap,
-                              int64_t bound, long long* count, hipStream_t s) {
-  hipError_t e = launch_zero_u64(reinterpret_cast<unsigned long long*>(count), 1, s);
-  if (e != hipSuccess || cap <= 0) return e;
-  hipLaunchKernelGGL(count_below_kernel, grid_for(cap), dim3(256), 0, s, set, size_dev, cap, bound,
-                     count);
-  return hipGetLastError();
-}
-
-hipError_t launch_remap(const int32_t* in, int64_t n, int64_t N, const int32_t* pos, int32_t* out,
+hipError_t launch_remap(const IdLists& in, int64_t N, const int32_t* pos, int32_t* out,
                         hipStream_t s) {
+  const int64_t n = list_size(in);
   if (n <= 0) return hipSuccess;
   ProfileScope prof(kKMinibatch, s);
   hipLaunchKernelGGL(remap_kernel, grid_for(n), dim3(256), 0, s, in, n, N, pos, out);
