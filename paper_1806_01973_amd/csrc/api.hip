@@ -644,8 +644,9 @@ static size_t walk_table_bytes(const pinsage_graph_t* g) {
 // table or NULL (read the CSR).
 static int run_walks(const pinsage_graph_t* graph, const pinsage_walk_params_t* walk,
                      const int32_t* sources, int64_t num_sources, pinsage_neighborhoods_t* out,
-                     unsigned long long* total_steps, const void* table, hipStream_t s) {
-  if (total_steps) {
+                     unsigned long long* total_steps, const void* table, hipStream_t s,
+                     bool steps_zeroed = false) {
+  if (total_steps && !steps_zeroed) {
     hipError_t e = launch_zero_u64(total_steps, 1, s);
     if (e != hipSuccess) return hip_fail(e, "step counter reset");
   }
@@ -1161,12 +1162,12 @@ int pinsage_embed_all(const pinsage_graph_t* graph, const pinsage_walk_params_t*
       if (!st && ov_table) {
         const hipError_t et = launch_walk_table(graph->row_offsets,
                                                 graph->offset_type == PINSAGE_I64, graph->col,
-                                                graph->nnz, n, ov_table, ov.walk);
+                                                graph->nnz, n, ov_table, ov.walk, total_steps);
         if (et != hipSuccess) st = hip_fail(et, "walk table launch");
       }
       if (!st)
         st = run_walks(graph, walk, nullptr, n, nbr_out, total_steps, gtab ? gtab : ov_table,
-                       ov.walk);
+                       ov.walk, ov_table != nullptr);
       const hipError_t e2 = hipEventRecord(ov.walk_done, ov.walk);
       // Join: the caller's stream waits for the walks before its share of
       // the transform, and for the side before the pool.
@@ -1189,11 +1190,12 @@ int pinsage_embed_all(const pinsage_graph_t* graph, const pinsage_walk_params_t*
     // region of the workspace (one read per edge step instead of two).
     if (tb && !gtab) {
       const hipError_t e = launch_walk_table(graph->row_offsets, graph->offset_type == PINSAGE_I64,
-                                             graph->col, graph->nnz, n, ws, s);
+                                             graph->col, graph->nnz, n, ws, s, total_steps);
       if (e != hipSuccess) return hip_fail(e, "walk table launch");
     }
     const void* tab = gtab ? gtab : (tb ? ws : nullptr);
-    if ((st = run_walks(graph, walk, nullptr, n, nbr_out, total_steps, tab, s))) return st;
+    if ((st = run_walks(graph, walk, nullptr, n, nbr_out, total_steps, tab, s, tb && !gtab)))
+      return st;
     if ((st = run_transform(L0, x, n, P, nullptr, n, ws, pre, s))) return st;
   }
 

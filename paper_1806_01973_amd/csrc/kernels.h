@@ -48,10 +48,11 @@ hipError_t launch_walk_topt(const WalkLaunch& a, hipStream_t s);
 // row start of col[e] (low, high 32 bits)}, degree 0 for an out-of-range id or
 // an empty or malformed row. A walk then takes one read per edge step instead
 // of an offset pair and a neighbour id. For graphs with nnz < 2^31 (degrees
-// fit 31 bits).
+// fit 31 bits). `zero`: a word the same launch clears (the walks' step counter).
 constexpr int64_t kWalkTableMaxNnz = 0x7FFFFFFFll;
 hipError_t launch_walk_table(const void* row_offsets, bool offsets64, const int32_t* col,
-                             int64_t nnz, int64_t num_nodes, void* table, hipStream_t s);
+                             int64_t nnz, int64_t num_nodes, void* table, hipStream_t s,
+                             unsigned long long* zero = nullptr);
 
 // Hard negative items (Sec. 3.3): out[i][j], j < k, drawn from ranks
 // [rank_lo, rank_hi) of the visit-count ranking of walks from queries[i].

@@ -266,7 +266,9 @@ __global__ __launch_bounds__(256) void walk_topt_kernel(WalkLaunch a) {
 
 template <typename OffT>
 __global__ void walk_table_kernel(const OffT* __restrict__ off, const int32_t* __restrict__ col,
-                                  int64_t nnz, int64_t num_nodes, uint4* __restrict__ table) {
+                                  int64_t nnz, int64_t num_nodes, uint4* __restrict__ table,
+                                  unsigned long long* zero) {
+  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0ull;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int32_t v = col[e];
@@ -333,7 +335,8 @@ hipError_t launch_walk_topt(const WalkLaunch& a, hipStream_t s) {
 }
 
 hipError_t launch_walk_table(const void* row_offsets, bool offsets64, const int32_t* col,
-                             int64_t nnz, int64_t num_nodes, void* table, hipStream_t s) {
+                             int64_t nnz, int64_t num_nodes, void* table, hipStream_t s,
+                             unsigned long long* zero) {
   if (nnz <= 0) return hipSuccess;
   if (nnz > kWalkTableMaxNnz) return hipErrorInvalidValue;
   ProfileScope prof(kKWalkTable, s);
@@ -342,10 +345,10 @@ hipError_t launch_walk_table(const void* row_offsets, bool offsets64, const int3
   uint4* t = static_cast<uint4*>(table);
   if (offsets64)
     hipLaunchKernelGGL(walk_table_kernel<int64_t>, grid, dim3(256), 0, s,
-                       static_cast<const int64_t*>(row_offsets), col, nnz, num_nodes, t);
+                       static_cast<const int64_t*>(row_offsets), col, nnz, num_nodes, t, zero);
   else
     hipLaunchKernelGGL(walk_table_kernel<int32_t>, grid, dim3(256), 0, s,
-                       static_cast<const int32_t*>(row_offsets), col, nnz, num_nodes, t);
+                       static_cast<const int32_t*>(row_offsets), col, nnz, num_nodes, t, zero);
   return hipGetLastError();
 }
 
