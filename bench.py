@@ -58,6 +58,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "node embeddings/sec (K=2 layerwise, all nodes) + walk steps/sec, 1 MI355X"
 HBM_PEAK_GBS = 8000.0
+# f32 is the fp32 MFMA rate; the kernels sum six bf16 MFMAs per fp32 product instead
+# (ceiling a sixth of the bf16 rate, 417), so their fraction of it can pass 1.
 MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 DEFAULT_STEPS = {"tiny": 20, "medium": 20, "minibatch": 20, "large": 4, "shard": 5, "hardneg": 20,
