@@ -27,24 +27,29 @@
 // or 16-byte (fp32) vector.
 //
 // fp32 storage: the matrix cores run bf16 16 times as fast as fp32, so every
-// operand is split exactly into three bf16 parts (split3) and the six products
+// operand is split exactly into three bf16 parts (split3) and the eight products
 // of parts that reach fp32's last bits run as bf16 MFMAs, the leading one and
-// the five small ones in accumulators of their own. That is no less precise
+// the seven small ones in accumulators of their own. That is no less precise
 // than the fp32 MFMA it replaces: relative error (2-norm, against 64 bits) of a
 // K = 256 product 0.9e-7 against 2.8e-7, K = 512 1.3e-7 against 4.0e-7, K = 768
 // with the row norm 1.0e-7 against 2.9e-7 (each MFMA rounds the running sum
-// once per 16 columns instead of once per 2; with all six in one accumulator it
-// is 2.4e-7). What bounds it: the MFMAs (48% busy at K = 256) beside the VALU work of
-// the splits, 44 instructions per 8 x 64 values, which fill most issue slots
-// the MFMAs leave when each tile splits both operands; a wave therefore covers
+// once per 16 columns instead of once per 2; with all in one accumulator it
+// is 2.4e-7), and a lone product is within 1.01 half units in the last place. With
+// six products (12% less time) the 2-norms are the same, but a lone product was up
+// to 1.7 half units off, where fp32 rounds it once.
+// Operands beyond the parts' range (split_covers) and sums that are not finite send
+// their tile through fp32 MFMAs as well, which take the elements concerned.
+// What bounds it: the MFMAs and the power they draw (64% busy at K = 256, at about
+// 1.7 of 2.4 GHz) beside the VALU work of the splits, 56 instructions per 8 x 64
+// values; a wave therefore covers
 // 64 x 64 (64 accumulators of each kind, two waves per SIMD), the next chunk is
 // split among the current one's MFMAs, and products of many rows read weights
 // that one small kernel split beforehand (split_b_kernel, PRE). 1M rows, 256 ->
-// 512: 2.34 ms (112 TFLOP/s) with fp32 MFMAs, 1.77 with both operands split in
-// the tiles, 1.62 (162 TFLOP/s) with B split before; 512 -> 256: 2.20, 1.62, 1.48;
-// 1.2M rows of the W layer (768 -> 256, norm): 4.12, 2.83, 2.48 (190 TFLOP/s).
+// 512: 2.34 ms (112 TFLOP/s) with fp32 MFMAs, 1.93 (136) so; 512 -> 256: 2.20,
+// 1.75; 1.2M rows of the W layer (768 -> 256, norm): 4.12, 3.09 (153 TFLOP/s). Looking
+// for the least magnitudes is 1-6% of that.
 // (The remainders as two-element bf16 dot products are fewer instructions, but
-// those run on the matrix pipe: 3.09 instead of 2.83.)
+// those run on the matrix pipe: 9% slower.)
 //
 // Epilogue: + bias, + an optional addend matrix (the pooled neighbour term
 // when W is split, see run_layer), ReLU (optional without L2), store in the
@@ -109,7 +114,11 @@ struct Cfg {
   static constexpr int STAGE_BYTES = GROUPS * kGroupBytes;
   static constexpr int RED_BYTES = L2 ? WAVES_N * BM * 4 : 0;
   static constexpr int BIAS_BYTES = BN * 4;
-  static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + RED_BYTES + BIAS_BYTES;
+  static constexpr int FLAG_BYTES = BF16 ? 0 : 16;  // fp32: some wave's results need a redo
+  static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + RED_BYTES + BIAS_BYTES + FLAG_BYTES;
+  // The redo's stages: A and B rows as they are, RAW_DPW row groups per wave.
+  static constexpr int RAW_DPW = ((BM + BN) / 16 + NWAVES - 1) / NWAVES;
+  static_assert(RAW_DPW * NWAVES <= GROUPS, "a raw stage fits the ring's");
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile is a multiple of 32x32");
   static_assert(STAGES >= 2 && PENDING <= 63, "vmcnt range");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of one workgroup");
@@ -183,6 +192,9 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   for (int c = tid; c < BN; c += THREADS)
     bias_s[c] = (a.bias && n0 + c < a.N) ? a.bias[n0 + c] : 0.0f;
   const int64_t ldb = a.ldb ? a.ldb : K;
+  int* const redo_s = reinterpret_cast<int*>(smem + C::LDS_BYTES - C::FLAG_BYTES);
+  if constexpr (!C::kBf16)
+    if (tid == 0) *redo_s = 0;
 
   // ---- DMA slots (fixed across the K loop) --------------------------------
   // Slot d of this wave fills group wave*DPW + d of every stage: A groups
@@ -193,31 +205,34 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   const unsigned char* const zrow = reinterpret_cast<const unsigned char*>(g_zero_row);
   const int64_t k0b = (int64_t)a.K0 * ESZ;
   const int nb32 = (a.N + 31) / 32;  // 32-row blocks of split B
-  const unsigned char* p0[ROW_DPW];
-  const unsigned char* p1[C::kTwoSources ? ROW_DPW : 1];
-#pragma unroll
-  for (int d = 0; d < ROW_DPW; ++d) {
-    const int grp = wave * ROW_DPW + d;
+  // This lane's row of a group, A groups [0, a_groups) first.
+  auto row_of_group = [&](int grp, int a_groups, const unsigned char*& q0,
+                          const unsigned char*& q1) __attribute__((always_inline)) {
     const int rr = lane >> 2;
-    if (C::PRE || grp < C::A_GROUPS) {
+    if (grp < a_groups) {
       const int64_t gr = m0 + grp * 16 + rr;
       const bool in_m = gr < a.M && grp < BM / 16;
       const int64_t src = !in_m ? -1 : (a.rowmap ? (int64_t)a.rowmap[gr] : gr);
-      p0[d] = (src >= 0 && src < a.rows_a0)
-                  ? static_cast<const unsigned char*>(a.A0) + src * a.lda0 * ESZ
-                  : zrow;
+      q0 = (src >= 0 && src < a.rows_a0)
+               ? static_cast<const unsigned char*>(a.A0) + src * a.lda0 * ESZ
+               : zrow;
       if constexpr (C::kTwoSources) {
         const unsigned char* q = (in_m && a.A1)
                                      ? static_cast<const unsigned char*>(a.A1) + gr * a.lda1 * ESZ
                                      : zrow;
-        p1[d] = reinterpret_cast<const unsigned char*>(reinterpret_cast<uintptr_t>(q) - k0b);
+        q1 = reinterpret_cast<const unsigned char*>(reinterpret_cast<uintptr_t>(q) - k0b);
       }
     } else {
-      const int r = n0 + (grp - C::A_GROUPS) * 16 + rr;
-      p0[d] = r < a.N ? static_cast<const unsigned char*>(a.B) + (int64_t)r * ldb * ESZ : zrow;
-      if constexpr (C::kTwoSources) p1[d] = p0[d];
+      const int r = n0 + (grp - a_groups) * 16 + rr;
+      q0 = r < a.N ? static_cast<const unsigned char*>(a.B) + (int64_t)r * ldb * ESZ : zrow;
+      if constexpr (C::kTwoSources) q1 = q0;
     }
-  }
+  };
+  const unsigned char* p0[ROW_DPW];
+  const unsigned char* p1[C::kTwoSources ? ROW_DPW : 1];
+#pragma unroll
+  for (int d = 0; d < ROW_DPW; ++d)
+    row_of_group(wave * ROW_DPW + d, C::A_GROUPS, p0[d], p1[C::kTwoSources ? d : 0]);
   const int kvec = vec_slot(lane >> 2, lane & 3) * VEC;
   const int nchunks = (K + BK - 1) / BK;
   // The large bf16 tiles start their K sweep at different chunks (rotation by
@@ -358,7 +373,7 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   } else {
     // fp32 storage: one k-step of 16 columns per chunk; half-wave h takes
     // columns 8h .. 8h+7 (vectors 2h, 2h+1) and splits them into bf16 triples.
-    f32x16 small[TM][TN];  // the five products below the leading one
+    f32x16 small[TM][TN];  // the products below the leading one
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -393,21 +408,23 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
             s.b[j].p[t] = *reinterpret_cast<const u32x4*>(
                 st + C::A_GROUPS * kGroupBytes + ((wn * TN + j) * 3 + t) * 1024 + 16 * lane);
     };
+    // Least magnitudes of the values this lane has split (split_b_kernel's for split B).
+    uint32_t key_a = ~0u, key_b = ~0u;
     auto split_raw = [&](const Raw& r, Parts& s) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) s.a[i] = split3(r.a[i][0], r.a[i][1]);
+      for (int i = 0; i < TM; ++i) s.a[i] = split3(r.a[i][0], r.a[i][1], key_a);
       if constexpr (!C::PRE)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) s.b[j] = split3(r.b[j][0], r.b[j][1]);
+        for (int j = 0; j < TN; ++j) s.b[j] = split3(r.b[j][0], r.b[j][1], key_b);
     };
     auto multiply = [&](const Parts& s) __attribute__((always_inline)) {
 #pragma unroll
-      for (int t = 0; t < 6; ++t)
+      for (int t = 0; t < kSplitProducts; ++t)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
-            if (t < 5) small[i][j] = mfma_split(s.b[j], s.a[i], t, small[i][j]);
+            if (t < kSplitProducts - 1) small[i][j] = mfma_split(s.b[j], s.a[i], t, small[i][j]);
             else acc[i][j] = mfma_split(s.b[j], s.a[i], t, acc[i][j]);
           }
     };
@@ -426,7 +443,8 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
       __builtin_amdgcn_sched_barrier(0);
       split_raw(r, nxt);
       multiply(cur);
-      constexpr int kMfma = 6 * TM * TN, kValu = 44 * (TM + (C::PRE ? 0 : TN));
+      constexpr int kMfma = kSplitProducts * TM * TN;
+      constexpr int kValu = 56 * (TM + (C::PRE ? 0 : TN));
 #pragma unroll
       for (int q = 0; q < kMfma; ++q) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                            // MFMA
@@ -454,50 +472,122 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] += small[i][j];
-    // Rows the split does not cover: an infinity (or a value that rounds to
-    // one) leaves NaN parts, and values below about 2^-110 lose their last
-    // part. Either shows in the lane's results, which are then summed again in
-    // plain fp32, a row at a time.
+    // What the split does not cover shows in the operands' least magnitudes, or, for
+    // infinities, NaN and values or sums that round to an infinity, in the results.
+    // Such elements are taken from the same product in fp32 MFMAs.
+    if constexpr (C::PRE) {
+      const uint32_t* const keys = reinterpret_cast<const uint32_t*>(
+          static_cast<const unsigned char*>(a.Bs) + (int64_t)nchunks * nb32 * 3072);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      float probe = 0.0f, big = 0.0f;
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          probe = fmaf(acc[i][j][e], 0.0f, probe);  // NaN unless all are finite
-          big = fmaxf(big, fabsf(acc[i][j][e]));
-        }
-      if (probe == 0.0f && (big == 0.0f || big >= 0x1p-64f)) continue;
-      const int64_t r = m0 + a_base_row + i * 32 + row_in_blk;
-      const int64_t src = r >= a.M ? -1 : (a.rowmap ? (int64_t)a.rowmap[r] : r);
-      const float* const ra = src >= 0 && src < a.rows_a0
-                                  ? static_cast<const float*>(a.A0) + src * a.lda0
-                                  : g_zero_row;
-      const float* const rb = C::kTwoSources && a.A1 && r < a.M
-                                  ? static_cast<const float*>(a.A1) + r * a.lda1 - a.K0
-                                  : g_zero_row;
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-#pragma unroll 1
-      for (int k = 0; k < K; ++k) {
-        const float x = k < a.K0 ? ra[k] : rb[k];
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int col = n0 + b_base_row + j * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
-            const float y =
-                col < a.N ? static_cast<const float*>(a.B)[(int64_t)col * ldb + k] : 0.0f;
-            acc[i][j][e] = fmaf(x, y, acc[i][j][e]);
-          }
+      for (int j = 0; j < TN; ++j) {
+        const int blk = (n0 + b_base_row) / 32 + j;
+        if (blk < nb32) key_b = umin(key_b, keys[blk]);
       }
     }
+    float probe = 0.0f;  // NaN unless all results are finite
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) probe = fmaf(acc[i][j][e], 0.0f, probe);
+    const bool covered = split_covers(wave_min_key(key_a), wave_min_key(key_b)) &&
+                         __ballot(probe != 0.0f) == 0ull;
+    if (!covered && lane == 0) *redo_s = 1;
   }
   wait_vmcnt<0>();  // drain the zero-row DMAs issued past the end
   __syncthreads();  // bias slice (and, below, row partials) visible
+
+  if constexpr (!C::kBf16) {
+    if (*redo_s) {
+      // The tile again with fp32 MFMAs (st of a chunk pairs half-wave h with its
+      // column 8h + st), two raw stages in the ring. Each element then follows from
+      // its own row and column alone: split where those are covered and the sum is
+      // finite, else fp32, so that it does not depend on the tile it lies in. About
+      // the time of the fp32 MFMA product on top, in the tiles that need it.
+      constexpr int RAW_DPW = C::RAW_DPW, RAW_A = BM / 16;
+      const unsigned char* q0[RAW_DPW];
+      const unsigned char* q1[C::kTwoSources ? RAW_DPW : 1];
+#pragma unroll
+      for (int d = 0; d < RAW_DPW; ++d)
+        row_of_group(wave * RAW_DPW + d, RAW_A, q0[d], q1[C::kTwoSources ? d : 0]);
+      auto issue_raw = [&](int c) __attribute__((always_inline)) {
+        const int kk = c * BK + kvec;
+        const uint32_t dst = smem_base + (uint32_t)((c & 1) * C::STAGE_BYTES) +
+                             (uint32_t)(wave * RAW_DPW * kGroupBytes);
+#pragma unroll
+        for (int d = 0; d < RAW_DPW; ++d) {
+          const unsigned char* p = q0[d];
+          if constexpr (C::kTwoSources) p = kk < a.K0 ? q0[d] : q1[d];
+          dma16(kk < K ? p + (int64_t)kk * ESZ : zrow,
+                __builtin_amdgcn_readfirstlane(dst + d * kGroupBytes));
+        }
+      };
+      f32x16 full[TM][TN];
+      uint32_t key_a[TM], key_b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) key_a[i] = ~0u;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) key_b[j] = ~0u;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) full[i][j][e] = 0.0f;
+      const int rb_off = RAW_A * kGroupBytes + frag_off(b_base_row + row_in_blk);
+      issue_raw(0);
+#pragma unroll 1
+      for (int c = 0; c < nchunks; ++c) {
+        wait_vmcnt<0>();
+        lds_barrier();  // chunk c is here; everybody is done with chunk c - 1
+        if (c + 1 < nchunks) issue_raw(c + 1);
+        const unsigned char* const st = smem + (c & 1) * C::STAGE_BYTES;
+        frag_t fa[TM][2], fb[TN][2];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          fa[i][0] = *reinterpret_cast<const frag_t*>(st + fa_off + i * 2 * kGroupBytes + voff0);
+          fa[i][1] = *reinterpret_cast<const frag_t*>(st + fa_off + i * 2 * kGroupBytes + voff1);
+          key_a[i] = least_key(fa[i][0], fa[i][1], key_a[i]);
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          fb[j][0] = *reinterpret_cast<const frag_t*>(st + rb_off + j * 2 * kGroupBytes + voff0);
+          fb[j][1] = *reinterpret_cast<const frag_t*>(st + rb_off + j * 2 * kGroupBytes + voff1);
+          key_b[j] = least_key(fb[j][0], fb[j][1], key_b[j]);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+              full[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                  __uint_as_float(fb[j][q >> 2][q & 3]), __uint_as_float(fa[i][q >> 2][q & 3]),
+                  full[i][j], 0, 0, 0);
+      }
+      // A lane's row of block i; the column of its element e of block j is lane
+      // 8 (e / 4) + 4 half + e % 4's.
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        key_a[i] = umin(key_a[i], (uint32_t)__shfl_xor((int)key_a[i], 32));
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        key_b[j] = umin(key_b[j], (uint32_t)__shfl_xor((int)key_b[j], 32));
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const uint32_t kb = (uint32_t)__shfl((int)key_b[j], 8 * (e >> 2) + 4 * half + (e & 3));
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+            const float x = acc[i][j][e];
+            const bool keep = split_covers(key_a[i], kb) && fabsf(x) < INFINITY;
+            acc[i][j][e] = keep ? x : full[i][j][e];
+          }
+        }
+      }
+      __syncthreads();  // the ring is free for the epilogue
+    }
+  }
 
   // ---- epilogue -----------------------------------------------------------
   // Lane l: output row m0 + a_base_row + 32i + l%32; for group g of tile j,
@@ -938,17 +1028,18 @@ __global__ __launch_bounds__(C::THREADS) void gemm_rs_kernel(GemmLaunch a) {
 
 // Bs: B [N][K] (row stride ldb) as bf16 triples in the order the fp32 kernel's
 // MFMAs read them: [k-step of 16][32-row block][part][lane] x 16 bytes, lane l
-// holding columns 8 (l / 32) .. + 7 of row l % 32; rows past N are zero.
-__global__ void split_b_kernel(const float* __restrict__ B, int64_t ldb, int N, int K,
-                               u32x4* __restrict__ Bs) {
-  const int nb32 = (N + 31) / 32;
-  const int64_t total = (int64_t)(K / 16) * nb32 * 64;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int lane = (int)(e & 63);
-    const int64_t blk = e >> 6;
-    const int nb = (int)(blk % nb32), ks = (int)(blk / nb32);
-    const int row = 32 * nb + (lane & 31);
+// holding columns 8 (l / 32) .. + 7 of row l % 32 (rows past N are zero), then each
+// 32-row block's least magnitude key. One workgroup per block of rows.
+constexpr int kSplitWaves = 16;
+__global__ __launch_bounds__(64 * kSplitWaves) void split_b_kernel(const float* __restrict__ B,
+                                                                   int64_t ldb, int N, int K,
+                                                                   u32x4* __restrict__ Bs) {
+  __shared__ uint32_t least[kSplitWaves];
+  const int nb32 = (N + 31) / 32, ksteps = K / 16;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = 32 * (int)blockIdx.x + (lane & 31);
+  uint32_t key = ~0u;
+  for (int ks = wave; ks < ksteps; ks += kSplitWaves) {
     u32x4 u = {0u, 0u, 0u, 0u}, v = u;
     if (row < N) {
       const u32x4* src =
@@ -956,9 +1047,17 @@ __global__ void split_b_kernel(const float* __restrict__ B, int64_t ldb, int N, 
       u = src[0];
       v = src[1];
     }
-    const Split3 s = split3(u, v);
+    const Split3 s = split3(u, v, key);
+    const int64_t blk = (int64_t)ks * nb32 + blockIdx.x;
 #pragma unroll
     for (int t = 0; t < 3; ++t) Bs[(blk * 3 + t) * 64 + lane] = s.p[t];
+  }
+  key = wave_min_key(key);
+  if (lane == 0) least[wave] = key;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kSplitWaves; ++w) key = umin(key, least[w]);
+    reinterpret_cast<uint32_t*>(Bs + (int64_t)ksteps * nb32 * 192)[blockIdx.x] = key;
   }
 }
 
@@ -1077,7 +1176,10 @@ bool launch_few(const GemmLaunch& a, hipStream_t s, hipError_t* e) {
 
 }  // namespace
 
-size_t split_b_bytes(int N, int K) { return (size_t)(K / 16) * ((N + 31) / 32) * 3072; }
+size_t split_b_bytes(int N, int K) {
+  const size_t blocks = (N + 31) / 32;
+  return (size_t)(K / 16) * blocks * 3072 + blocks * 4;
+}
 
 hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
@@ -1088,8 +1190,7 @@ hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s) {
   if (use_rs(a)) return launch_rs(a, s);
   if (a.bf16) return launch_bf16(a, s);
   if (!a.Bs) return launch_f32<false>(a, s);
-  const int64_t units = (int64_t)((a.K0 + a.K1) / 16) * ((a.N + 31) / 32) * 64;
-  hipLaunchKernelGGL(split_b_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL(split_b_kernel, dim3((unsigned)((a.N + 31) / 32)), dim3(64 * kSplitWaves), 0, s,
                      static_cast<const float*>(a.B), a.ldb ? a.ldb : (int64_t)a.K0 + a.K1, a.N,
                      a.K0 + a.K1, static_cast<u32x4*>(a.Bs));
   const hipError_t e = hipGetLastError();

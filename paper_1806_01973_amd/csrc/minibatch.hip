@@ -184,13 +184,14 @@ __device__ __forceinline__ auto load_parts(const void* table, int64_t row, int d
         }
       }
     }
-    return split3(u, v);
+    uint32_t key = ~0u;
+    return split3(u, v, key);
   }
 }
 
 // Eq. (1) per pair. A block of 8 waves scores 16 queries against all the
 // negatives on the matrix cores (v_mfma_f32_16x16x32_bf16; fp32 storage as
-// split triples, six MFMAs per product): the queries' operand parts sit in LDS,
+// split triples, eight MFMAs per product): the queries' operand parts sit in LDS,
 // wave w takes negatives 16 (w + 8 i) .. + 15 and reads their rows straight
 // from memory as operands (the negatives are shared by every block and stay in
 // L2). A lane then holds one query's scores of 4 negatives; it adds its hinge
@@ -284,8 +285,8 @@ __global__ __launch_bounds__(512) void loss_pairs_kernel(LossLaunch a) {
                                                       0);
         } else {
 #pragma unroll
-          for (int i = 0; i < 6; ++i) {
-            f32x4& c = i < 5 ? small : s;
+          for (int i = 0; i < kSplitProducts; ++i) {
+            f32x4& c = i < kSplitProducts - 1 ? small : s;
             c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                 __builtin_bit_cast(bf16x8, f[u].p[split_b(i)]),
                 __builtin_bit_cast(bf16x8, q[64 * split_a(i)]), c, 0, 0, 0);
