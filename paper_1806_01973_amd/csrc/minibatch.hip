@@ -154,9 +154,11 @@ __device__ __forceinline__ float load_elem(const void* base, int64_t i) {
 
 // Elements k0 .. k0 + 7 of row `row` of a [rows][d] table as MFMA operand
 // parts: the bf16 values themselves, or fp32 values split exactly into three
-// bf16 parts. Zeros for row < 0 and past d. VEC: rows are whole 16-byte vectors.
+// bf16 parts (key: their least magnitude so far). Zeros for row < 0 and past d.
+// VEC: rows are whole 16-byte vectors.
 template <bool BF16, bool VEC>
-__device__ __forceinline__ auto load_parts(const void* table, int64_t row, int d, int k0) {
+__device__ __forceinline__ auto load_parts(const void* table, int64_t row, int d, int k0,
+                                           uint32_t& key) {
   if constexpr (BF16) {
     u32x4 v = {0u, 0u, 0u, 0u};
     if (row < 0 || k0 >= d) return v;
@@ -184,9 +186,24 @@ __device__ __forceinline__ auto load_parts(const void* table, int64_t row, int d
         }
       }
     }
-    uint32_t key = ~0u;
     return split3(u, v, key);
   }
+}
+
+// fp32 elements k0 .. k0 + 3 of row `row`, zeros as above.
+template <bool VEC>
+__device__ __forceinline__ u32x4 load4_f32(const void* table, int64_t row, int d, int k0) {
+  u32x4 u = {0u, 0u, 0u, 0u};
+  if (row < 0 || k0 >= d) return u;
+  const float* src = static_cast<const float*>(table) + row * d + k0;
+  if constexpr (VEC) {
+    u = *reinterpret_cast<const u32x4*>(src);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (k0 + e < d) u[e] = __float_as_uint(src[e]);
+  }
+  return u;
 }
 
 // Eq. (1) per pair. A block of 8 waves scores 16 queries against all the
@@ -211,21 +228,26 @@ __global__ __launch_bounds__(512) void loss_pairs_kernel(LossLaunch a) {
   __shared__ u32x4 qf[KS * PARTS * 64];
   __shared__ float pos_s[QB], hard_s[QB], sum_s[WAVES][QB];
   __shared__ int count_s[QB];
+  __shared__ uint32_t key_s[QB];  // fp32: least magnitude of each query
   const int d = a.d, ksteps = (d + 31) / 32;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int64_t b0 = (int64_t)blockIdx.x * QB;
   auto row_of = [](const int32_t* map, int64_t i) { return map ? (int64_t)map[i] : i; };
 
+  if (!BF16 && t < QB) key_s[t] = ~0u;
+  if constexpr (!BF16) __syncthreads();
   // Queries as operands: lane l of k-step ks holds row l % 16, columns
   // 32 ks + 8 (l / 16) .. + 7 (zeros for missing pairs or ids).
   for (int i = t; i < (ksteps + U - 1) / U * U * 64; i += 512) {
     const int64_t b = b0 + (i & 15);
     const int64_t row = b < a.B ? row_of(a.q_rows, b) : -1;
-    const auto f = load_parts<BF16, VEC>(a.zq, row, d, 32 * (i >> 6) + 8 * ((i >> 4) & 3));
+    uint32_t key = ~0u;
+    const auto f = load_parts<BF16, VEC>(a.zq, row, d, 32 * (i >> 6) + 8 * ((i >> 4) & 3), key);
     if constexpr (BF16) {
       qf[i] = f;
     } else {
+      atomicMin(&key_s[i & 15], key);
 #pragma unroll
       for (int p = 0; p < 3; ++p) qf[((i >> 6) * 3 + p) * 64 + (i & 63)] = f.p[p];
     }
@@ -265,17 +287,20 @@ __global__ __launch_bounds__(512) void loss_pairs_kernel(LossLaunch a) {
   __syncthreads();
 
   const float shift = a.margin - pos_s[lane & 15];
+  uint32_t key_q = ~0u;  // of the block's queries
+  if constexpr (!BF16) key_q = wave_min_key(key_s[lane & 15]);
   float acc = 0.0f;
   for (int64_t n0 = 16 * wave; n0 < a.n_neg; n0 += 16 * WAVES) {
     const int64_t n = n0 + (lane & 15);
     const int64_t row = n < a.n_neg ? row_of(a.neg_rows, n) : -1;
     f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f}, small = s;
+    uint32_t key = ~0u;
     // U k-steps' rows in flight before the first is multiplied.
     for (int ks0 = 0; ks0 < ksteps; ks0 += U) {
-      decltype(load_parts<BF16, VEC>(a.zneg, row, d, 0)) f[U];
+      decltype(load_parts<BF16, VEC>(a.zneg, row, d, 0, key)) f[U];
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        f[u] = load_parts<BF16, VEC>(a.zneg, row, d, 32 * (ks0 + u) + 8 * (lane >> 4));
+        f[u] = load_parts<BF16, VEC>(a.zneg, row, d, 32 * (ks0 + u) + 8 * (lane >> 4), key);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const u32x4* q = qf + (ks0 + u) * PARTS * 64 + lane;
@@ -294,23 +319,41 @@ __global__ __launch_bounds__(512) void loss_pairs_kernel(LossLaunch a) {
         }
       }
     }
+    if constexpr (!BF16) {
+      s += small;
+      // Scores whose rows the parts do not cover, and those that are not finite, are
+      // taken from the same 16 x 16 scores in fp32 MFMAs (step e of 16 columns pairs
+      // lane group l / 16 with column 4 (l / 16) + e).
+      float probe = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) probe = fmaf(s[r], 0.0f, probe);
+      if (!split_covers(key_q, wave_min_key(key)) || __ballot(probe != 0.0f) != 0ull) {
+        const int64_t bq = b0 + (lane & 15);
+        const int64_t rq = bq < a.B ? row_of(a.q_rows, bq) : -1;
+        f32x4 full = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+        for (int k0 = 4 * (lane >> 4); k0 - 4 * (lane >> 4) < d; k0 += 16) {
+          const u32x4 y = load4_f32<VEC>(a.zneg, row, d, k0), x = load4_f32<VEC>(a.zq, rq, d, k0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            full = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(y[e]),
+                                                        __uint_as_float(x[e]), full, 0, 0, 0);
+        }
+        key = umin(key, (uint32_t)__shfl_xor((int)key, 16));
+        key = umin(key, (uint32_t)__shfl_xor((int)key, 32));  // of negative n0 + l % 16
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const uint32_t kn = (uint32_t)__shfl((int)key, 4 * (lane >> 4) + r);
+          const bool keep = split_covers(key_s[lane & 15], kn) && fabsf(s[r]) < INFINITY;
+          s[r] = keep ? s[r] : full[r];
+        }
+      }
+    }
     // Lane l: query l % 16, negatives n0 + 4 (l / 16) + 0..3.
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int64_t nr = n0 + 4 * (lane >> 4) + r;
-      float x = s[r] + small[r];
-      if constexpr (!BF16) {
-        // What the split does not cover (an infinity leaves NaN parts, tiny
-        // values lose their last part) is summed again in plain fp32.
-        const bool fine = fabsf(x) < INFINITY && (x == 0.0f || fabsf(x) >= 0x1p-64f);
-        if (!fine && nr < a.n_neg && b0 + (lane & 15) < a.B) {
-          const int64_t rn = row_of(a.neg_rows, nr), rq = row_of(a.q_rows, b0 + (lane & 15));
-          x = 0.0f;
-          if (rn >= 0 && rq >= 0)
-            for (int k = 0; k < d; ++k)
-              x = fmaf(load_elem<false>(a.zq, rq * d + k), load_elem<false>(a.zneg, rn * d + k), x);
-        }
-      }
+      const float x = s[r];
       const float h = x + shift;
       acc += (nr < a.n_neg && h > 0.0f) ? h : 0.0f;
     }

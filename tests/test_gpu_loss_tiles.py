@@ -51,3 +51,46 @@ def test_loss_with_infinite_and_huge_rows():
     ng[4, 5] = float("inf")
     _, per = ps.max_margin_loss(q.cuda(), p.cuda(), ng.cuda(), 0.1)
     assert torch.isinf(per).all()
+
+
+def test_scores_of_values_at_the_ends_of_the_range():
+    """Tiny queries against huge negatives and the other way round, tiny values beside
+    ordinary ones, an infinite and a NaN row among others; also in rows that are not whole
+    vectors. Each score has fp32's error, (d + 8) 2^-24 of the summed magnitudes."""
+    import paper_1806_01973_amd as ps
+    for d in (64, 65):
+        gen = torch.Generator().manual_seed(d)
+        q, p, ng = (torch.randn((n, d), generator=gen) for n in (20, 20, 40))
+        p *= 0.0
+        ng[:, :4] = 0.0
+        q[3] *= 2.0 ** -120
+        ng[5] = 0.0
+        ng[5, 0] = 2.0 ** 115
+        q[4, 0] = 1.2345 * 2.0 ** -130  # against ng[5]: the lone product 1.2e-5
+        q[:, 0] = torch.where(torch.arange(20) == 4, q[:, 0], 0.0)
+        q[:, 1] = torch.where(torch.arange(20) == 7, 2.0 ** 120, 0.0)
+        ng[6, 1] = 1.2345 * 2.0 ** -125
+        s = q.double() @ ng.double().t()  # (the positives are zero rows)
+        mag = q.double().abs() @ ng.double().abs().t()
+        _, per = ps.max_margin_loss(q.cuda(), p.cuda(), ng.cuda(), 0.1)
+        ref = torch.relu(s + 0.1).mean(1)
+        tol = (d + 8) * 2.0 ** -24 * mag.mean(1) + 48 * 2.0 ** -24 * (ref + 0.1)
+        assert ((per.double().cpu() - ref).abs() <= tol).all()
+        # One negative at a time, so that no other term hides its score.
+        for n in (5, 6):
+            _, one = ps.max_margin_loss(q.cuda(), p.cuda(), ng[n:n + 1].cuda(), 0.0)
+            tol1 = (d + 8) * 2.0 ** -24 * mag[:, n] + 2.0 ** -149
+            assert ((one.double().cpu() - torch.relu(s[:, n])).abs() <= tol1).all(), n
+        # An infinite negative moves every pair to infinity or leaves its term at 0; a NaN
+        # query has only zero terms; the others keep their bits.
+        q2 = q.clone()
+        q2[11, 9] = float("nan")
+        _, per2 = ps.max_margin_loss(q2.cuda(), p.cuda(), ng.cuda(), 0.1)
+        assert float(per2[11]) == 0.0
+        keep = torch.arange(20) != 11
+        assert torch.equal(per2.cpu()[keep], per.cpu()[keep])
+        ng2 = ng.clone()
+        ng2[30, 20] = float("inf")
+        _, per3 = ps.max_margin_loss(q.cuda(), p.cuda(), ng2.cuda(), 0.1)
+        up = q[:, 20] > 0
+        assert torch.isinf(per3.cpu()[up]).all() and torch.isfinite(per3.cpu()[~up]).all()
