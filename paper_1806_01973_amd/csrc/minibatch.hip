@@ -6,6 +6,8 @@
 //    Sec. 3.3, done on the device);
 //  * the max-margin loss of Eq. 1 over a shared negative set.
 // Everything is integer or fixed-order fp32, hence deterministic.
+#include <type_traits>
+
 #include "device_util.h"
 #include "kernels.h"
 #include "split_device.h"
@@ -152,6 +154,26 @@ __device__ __forceinline__ float load_elem(const void* base, int64_t i) {
   else return static_cast<const float*>(base)[i];
 }
 
+// The 16-byte vector at element i, and s + the dot product of two in index order.
+template <bool BF16>
+__device__ __forceinline__ u32x4 load_vec(const void* base, int64_t i) {
+  return *reinterpret_cast<const u32x4*>(static_cast<const unsigned char*>(base) +
+                                         i * (BF16 ? 2 : 4));
+}
+template <bool BF16>
+__device__ __forceinline__ float dot_vec(const u32x4& x, const u32x4& y, float s) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if constexpr (BF16) {
+      s = fmaf(__uint_as_float(x[q] << 16), __uint_as_float(y[q] << 16), s);
+      s = fmaf(__uint_as_float(x[q] & 0xFFFF0000u), __uint_as_float(y[q] & 0xFFFF0000u), s);
+    } else {
+      s = fmaf(__uint_as_float(x[q]), __uint_as_float(y[q]), s);
+    }
+  }
+  return s;
+}
+
 // Elements k0 .. k0 + 7 of row `row` of a [rows][d] table as MFMA operand
 // parts: the bf16 values themselves, or fp32 values split exactly into three
 // bf16 parts (key: their least magnitude so far). Zeros for row < 0 and past d.
@@ -213,12 +235,13 @@ __device__ __forceinline__ u32x4 load4_f32(const void* table, int64_t row, int d
 // from memory as operands (the negatives are shared by every block and stay in
 // L2). A lane then holds one query's scores of 4 negatives; it adds its hinge
 // terms in order, the 4 lanes of a query are summed by a fixed butterfly and
-// the waves in order. The positive and the pair's own hard negatives are dot
-// products of 32 threads each, summed by a fixed butterfly.
+// the waves in order. The positive is a dot product of 32 threads, the pair's own
+// hard negatives of 8 each, summed by fixed butterflies.
 // What bounds it: the latency of the rows' reads. 2,048 pairs, 500 negatives,
-// d = 256, with the mean's launch: 16.8 us in bf16 and 27.1 in fp32, where fp32
-// FMAs from LDS took 47.0 and 49.7; with 4 hard negatives per pair 20.8 (50.6);
-// 4,096 pairs, 1,000 + 7 negatives, d = 512: 72 (340).
+// d = 256, with the mean's launch: 15.8 us in bf16 and 26.1 in fp32, where fp32
+// FMAs from LDS took 47.0 and 49.7; with 4 hard negatives per pair 16.4 (50.6), with
+// 64 28.6 (56.2); 256 pairs with 1,000 each 157 (183, fp32 246 and 287);
+// 4,096 pairs, 1,000 + 16 negatives, d = 512: 50 (345).
 // KS: most k-steps of 32 columns; TPQ threads per query.
 template <bool BF16, bool VEC, int KS>
 __global__ __launch_bounds__(512) void loss_pairs_kernel(LossLaunch a) {
@@ -267,16 +290,76 @@ __global__ __launch_bounds__(512) void loss_pairs_kernel(LossLaunch a) {
       return s;
     };
     const float pos = dot(a.zpos, b < a.B ? row_of(a.pos_rows, b) : -1);
+    // Hard negatives: 8 threads per row, 4 U rows of the query at a time, all their
+    // reads in flight at once (absent rows read row 0, so that no read waits for a
+    // branch). One row after another by 32 threads each, 1,000 per pair took 2.1-3.3
+    // ms in 256 pairs; one row per thread, 0.29-0.58.
     float hh = 0.0f;
     int hv = 0;
-    if (b < a.B) {
-      for (int64_t j = 0; j < a.k_hard; ++j) {
-        const int64_t row = row_of(a.hard_rows, b * a.k_hard + j);
-        if (row < 0) continue;
-        const float h = dot(a.zhard, row) - pos + a.margin;
-        hh += h > 0.0f ? h : 0.0f;
-        ++hv;
+    auto hard = [&](auto rows_per_group, auto vectors) __attribute__((always_inline)) {
+      constexpr int U = decltype(rows_per_group)::value;
+      const int gl = c & 7, gr = c >> 3;
+      for (int64_t j0 = gr; j0 - gr < a.k_hard; j0 += 4 * U) {
+        int64_t rows[U], at[U];
+        float s[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int64_t j = j0 + 4 * u;
+          rows[u] = b < a.B && j < a.k_hard ? row_of(a.hard_rows, b * a.k_hard + j) : -1;
+          at[u] = (rows[u] < 0 ? 0 : rows[u]) * d;
+          s[u] = 0.0f;
+        }
+        if (qr >= 0) {
+          if constexpr (decltype(vectors)::value) {
+            constexpr int VE = BF16 ? 8 : 4;
+#pragma unroll 2
+            for (int k = VE * gl; k < d; k += 8 * VE) {
+              u32x4 y[U];
+#pragma unroll
+              for (int u = 0; u < U; ++u) y[u] = load_vec<BF16>(a.zhard, at[u] + k);
+              const u32x4 x = load_vec<BF16>(a.zq, qr * d + k);
+#pragma unroll
+              for (int u = 0; u < U; ++u) s[u] = dot_vec<BF16>(x, y[u], s[u]);
+            }
+          } else {
+#pragma unroll 2
+            for (int k = gl; k < d; k += 8) {
+              float y[U];
+#pragma unroll
+              for (int u = 0; u < U; ++u) y[u] = load_elem<BF16>(a.zhard, at[u] + k);
+              const float x = load_elem<BF16>(a.zq, qr * d + k);
+#pragma unroll
+              for (int u = 0; u < U; ++u) s[u] = fmaf(x, y[u], s[u]);
+            }
+          }
+        }
+#pragma unroll
+        for (int o = 4; o >= 1; o >>= 1)
+#pragma unroll
+          for (int u = 0; u < U; ++u) s[u] += __shfl_xor(s[u], o);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float h = s[u] - pos + a.margin;
+          hh += rows[u] >= 0 && h > 0.0f ? h : 0.0f;
+          hv += rows[u] >= 0 ? 1 : 0;
+        }
       }
+#pragma unroll
+      for (int o = TPQ / 2; o >= 8; o >>= 1) {
+        hh += __shfl_xor(hh, o);
+        hv += __shfl_xor(hv, o);
+      }
+    };
+    // Whole vectors where both tables start on one; these rows may come from anywhere.
+    const uintptr_t starts = reinterpret_cast<uintptr_t>(a.zq) | reinterpret_cast<uintptr_t>(a.zhard);
+    const std::integral_constant<int, 1> few{};
+    const std::integral_constant<int, 4> many{};
+    if (VEC && starts % 16 == 0) {
+      if (a.k_hard > 4) hard(many, std::integral_constant<bool, VEC>{});
+      else if (a.k_hard > 0) hard(few, std::integral_constant<bool, VEC>{});
+    } else {
+      if (a.k_hard > 4) hard(many, std::false_type{});
+      else if (a.k_hard > 0) hard(few, std::false_type{});
     }
     if (c == 0) {
       pos_s[q] = pos;
