@@ -5,14 +5,16 @@
 // random.
 //
 // One workgroup of 1024 threads owns one query at a time (grid-stride over
-// queries); everything stays in LDS (4.25 B per visit slot) and 64 registers, so
+// queries); everything stays in LDS (70 KB at 16,384 visit slots) and 64 registers, so
 // that two workgroups share a CU and one's sorts (VALU work) run under the
 // other's walks (random reads, which bound the kernel): 2,048 queries of 4,096 x 4
-// landings take 1.16 ms, 1.03 of it walks, where one workgroup per CU with a
-// second table of 4 B per slot for the ranked ids took 1.27. No such table: the
-// repeated pins are at most half the slots, so their keys and ids fit the sorted
-// visits' space, and a draw of a pin visited once is written by the thread that
-// holds it in registers.
+// landings on the 1.2M-node graph take 1.11 ms, nearly all of it walks, where one
+// workgroup per CU with a second table of 4 B per slot for the ranked ids took 1.27.
+// No such table: the pins visited once pass through the sorted visits' space before
+// the repeated ones, which are at most half the slots, take it for their keys and
+// ids. (Held in registers and searched for by each draw, as they also were: 1.16 ms,
+// and more with each draw, 3.1 at 5,000 per query, where this takes 1.03.) The widest
+// form keeps 13 of its registers in scratch (52 bytes a lane).
 //   1. walks: thread t runs walks t, t + 1024, ...; walk w
 //      writes its pin landings into slots [w*hops, (w+1)*hops); the rest of
 //      the slots is empty;
@@ -383,15 +385,39 @@ __global__ __launch_bounds__(kThreads, SHARE ? 8 : 4) void hard_negative_kernel(
           f(e, (uint32_t)(first + e - head + 1));
       }
     };
-    int nmulti = 0, nsingle = 0;
-    tails([&](int, uint32_t c) __attribute__((always_inline)) {
-      nmulti += c > 1u ? 1 : 0;
-      nsingle += c == 1u ? 1 : 0;
-    });
-    int Dm = 0, Ds = 0;  // pins visited more than once, and once
-    const int p0 = block_exclusive_sum(nmulti, wave, lane, wave_tot, &Dm);
-    const int s0 = block_exclusive_sum(nsingle, wave, lane, wave_tot, &Ds);
-    const int D = Dm + Ds;
+    // Pins visited more than once and once, in the halves of a word (at most 2^13
+    // and 2^14) so that one scan numbers both.
+    int pins = 0, all = 0;
+    tails([&](int, uint32_t c) __attribute__((always_inline)) { pins += c > 1u ? 1 << 16 : 1; });
+    const int before = block_exclusive_sum(pins, wave, lane, wave_tot, &all);
+    const int p0 = before >> 16, s0 = before & 0xFFFF;
+    const int Dm = all >> 16, D = Dm + (all & 0xFFFF);
+    const int64_t top = D < a.rank_hi ? (int64_t)D : (int64_t)a.rank_hi;
+    const int64_t n = top - a.rank_lo;
+    int32_t* out = a.out + qi * (int64_t)a.k;
+    auto rank_of = [&](int j) __attribute__((always_inline)) {
+      const uint4 r = philox4x32_10(make_uint4((uint32_t)u, (uint32_t)j, 0u, 1u), k0, k1);
+      return a.rank_lo + (int)(((uint64_t)r.x * (uint64_t)n) >> 32);
+    };
+
+    // Draws that fall on a pin visited once: rank Dm + s is the s-th such pin in
+    // id order. The visits' space (only the registers hold them now) takes those
+    // pins in that order, padded as the sorts are, until the draws are made.
+    if (n > 0 && top > Dm) {
+      int s = s0;
+      tails([&](int e, uint32_t c) __attribute__((always_inline)) {
+        if (c == 1u) {
+          keys[padded<E>(s)] = k[e];
+          ++s;
+        }
+      });
+      __syncthreads();
+      for (int j = tid; j < a.k; j += kThreads) {
+        const int rank = rank_of(j);
+        if (rank >= Dm) out[j] = (int32_t)keys[padded<E>(rank - Dm)];
+      }
+      __syncthreads();
+    }
     {
       int p = p0;
       tails([&](int e, uint32_t c) __attribute__((always_inline)) {
@@ -401,40 +427,6 @@ __global__ __launch_bounds__(kThreads, SHARE ? 8 : 4) void hard_negative_kernel(
           ++p;
         }
       });
-    }
-
-    // Draws that fall on a pin visited once: rank Dm + s is the s-th such pin in
-    // id order, which the thread holding it writes from its registers. Each wave
-    // looks at 64 draws at a time and visits those in its own range.
-    const int64_t top = D < a.rank_hi ? (int64_t)D : (int64_t)a.rank_hi;
-    const int64_t n = top - a.rank_lo;
-    int32_t* out = a.out + qi * (int64_t)a.k;
-    auto rank_of = [&](int j) __attribute__((always_inline)) {
-      const uint4 r = philox4x32_10(make_uint4((uint32_t)u, (uint32_t)j, 0u, 1u), k0, k1);
-      return a.rank_lo + (int)(((uint64_t)r.x * (uint64_t)n) >> 32);
-    };
-    if (n > 0) {
-      const int s1 = s0 + nsingle;  // this thread's pins visited once: [s0, s1)
-      const int w0 = __builtin_amdgcn_readfirstlane(s0);
-      const int w1 = __builtin_amdgcn_readlane(s1, kWave - 1);
-      for (int j0 = 0; j0 < a.k; j0 += kWave) {
-        int want = -1;
-        if (j0 + lane < a.k) want = rank_of(j0 + lane) - Dm;
-        uint64_t mine = __ballot(want >= w0 && want < w1);
-        while (mine) {
-          const int l = __builtin_ctzll(mine);
-          mine &= mine - 1;
-          const int target = __builtin_amdgcn_readlane(want, l);
-          if (target < s0 || target >= s1) continue;
-          int s = s0;
-          tails([&](int e, uint32_t c) __attribute__((always_inline)) {
-            if (c == 1u) {
-              if (s == target) out[j0 + l] = (int32_t)k[e];
-              ++s;
-            }
-          });
-        }
-      }
     }
     const int sort_n = Dm > 0 ? sort_size(Dm) : 0;
 #pragma unroll
@@ -449,7 +441,7 @@ __global__ __launch_bounds__(kThreads, SHARE ? 8 : 4) void hard_negative_kernel(
     if (Dm > 0) lg_sort = block_sort_upto<kMultiE>(keys, Dm, wave, lane);
 
     // ---- 5. draws from the window that fall on a repeated pin ---------------
-    for (int j = tid; j < a.k; j += kThreads) {
+    for (int j = n > 0 && Dm <= a.rank_lo ? a.k : tid; j < a.k; j += kThreads) {
       if (n <= 0) {
         out[j] = -1;
         continue;

@@ -49,3 +49,15 @@ def test_few_and_many_distinct_pins(orc, walks, hops):
     off, col = synth.csr_from_edges(P, 1, np.stack([np.arange(P), np.zeros(P, np.int64)], 1))
     q = np.array([0, 7, P - 1, P], np.int32)
     _check(orc, off, col, P, 1, q, 70, walks, hops, 100, 20_000)
+
+
+@pytest.mark.parametrize("nq", [7, 300])
+@pytest.mark.parametrize("lo,hi", [(0, 40_000), (0, 300), (6_000, 40_000)])
+def test_many_draws_per_query(orc, graph, nq, lo, hi):
+    """More draws than threads, over the whole ranking, over pins visited more than once
+    alone, and over pins visited once alone."""
+    P, B, off, col = graph
+    print(f"[case] many draws nq={nq} lo={lo} hi={hi}", flush=True)
+    q = np.random.default_rng(nq).integers(0, P, nq).astype(np.int32)
+    for k, walks, hops in ((1025, 500, 2), (2100, 4096, 4)):
+        _check(orc, off, col, P, B, q, k, walks, hops, lo, hi)
