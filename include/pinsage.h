@@ -299,7 +299,8 @@ int pinsage_convolve_workspace_size(const pinsage_layer_t* layer, int64_t n_tran
 /* One CONVOLVE layer (Algorithm 1) in the layer-wise dataflow (Sec. 3.4):
  *   P[i]  = ReLU(Q h_in[t(i)] + q)             for i in [0, n_transform),
  *           t(i) = transform_rows[i] or i
- *   n[r]  = sum_t weights[r][t] * P[idx[r][t]] (rank order; padding skipped)
+ *   n[r]  = sum_t weights[r][t] * P[idx[r][t]] (fp32; padding skipped; in an
+ *           order that follows from the shapes and ids alone)
  *   z[r]  = ReLU(W concat(h_in[s(r)], n[r]) + w),  s(r) = self_rows[r] or r
  *   h_out[r] = z[r] / ||z[r]||_2 (a zero z stays zero)   for r in [0, n_out)
  * (with DENSE_THEN_POOL, n[r] is never formed: the pool runs over rows of
@@ -310,7 +311,9 @@ int pinsage_convolve_workspace_size(const pinsage_layer_t* layer, int64_t n_tran
  * transform_rows, self_rows: device int32 row maps into h_in, or NULL for the
  * identity (entries outside [0, n_in) read as zero rows). Without
  * transform_rows, n_transform <= n_in; without self_rows, n_out <= n_in.
- * workspace: device, >= pinsage_convolve_workspace_size bytes, 256-aligned. */
+ * workspace: device, >= pinsage_convolve_workspace_size bytes, 256-aligned (as is
+ * every workspace below: one that is short by no more than the room for fp32
+ * weights split beforehand is accepted, and gives the same bits more slowly). */
 int pinsage_convolve_layer(const pinsage_layer_t* layer, const void* h_in, int64_t n_in,
                            int64_t n_transform, const int32_t* transform_rows,
                            const pinsage_neighborhoods_t* nbr, const int32_t* self_rows,
@@ -348,7 +351,9 @@ int pinsage_schedule_destroy(pinsage_schedule_t* schedule);
  * the library, one per GPU, held until the process ends; the call itself
  * allocates nothing. Arguments, layout and results are those of
  * pinsage_convolve_layer (same kernels, bit-identical output). A layer whose
- * workspace (pinsage_convolve_workspace_size) exceeds the scratch returns
+ * workspace exceeds the scratch (not counting the room for fp32 weights split
+ * beforehand, which pinsage_convolve_workspace_size includes and a call can do
+ * without) returns
  * PINSAGE_EUNSUPPORTED and launches nothing. The scratch keeps the last call's
  * contents (every region a call reads is written earlier in that call), and
  * all calls on one GPU share it: calls that overlap on one GPU (two streams,

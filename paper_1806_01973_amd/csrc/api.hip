@@ -225,16 +225,14 @@ int check_nbr(const pinsage_neighborhoods_t* n, int64_t rows, const char* what) 
 //   DENSE_THEN_POOL, bf16, d_in = d_out = 256: + W_s as product fragments for
 //                    the fused pool and W kernel (used when top_t <= 64; the
 //                    pooled chunk then stays unused).
-//   When `pre` and the pool may take column slabs: + its choice (one int).
 //   fp32, when `pre`: + Q's, W_n's and W's (or W_s's) splits, Q's and W_n's
 //                    twice (one per stream of the overlapped schedule).
 struct LayerWs {
   size_t table = 0, pchunk = 0, pooled = 0, wsp = 0;
-  size_t qs = 0, wns = 0, wss = 0, choice = 0;
+  size_t qs = 0, wns = 0, wss = 0;
   bool chained = false;
   size_t base() const { return table + pchunk + pooled + wsp; }
-  size_t choice_at() const { return base() + 2 * (qs + wns) + wss; }
-  size_t total() const { return choice_at() + choice; }
+  size_t total() const { return base() + 2 * (qs + wns) + wss; }
 };
 
 bool chained_layer(const pinsage_layer_t* L) {
@@ -264,8 +262,6 @@ LayerWs layer_ws(const pinsage_layer_t* L, int64_t n_transform, int64_t n_out, b
     w.qs = split_ws(L->dtype, n_transform, L->m, L->d_in);
     if (split) w.wns = split_ws(L->dtype, n_transform, L->d_out, L->m);
     w.wss = split_ws(L->dtype, n_out, L->d_out, split ? L->d_in : L->d_in + L->m);
-    if (!w.wsp && pool_slabs_wanted(n_transform, (int64_t)(split ? L->d_out : L->m) * es, n_out))
-      w.choice = kAlign;
   }
   return w;
 }
@@ -428,9 +424,18 @@ int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
     if (e != hipSuccess) return hip_fail(e, "pool and W launch");
     return PINSAGE_OK;
   }
+  // The pool's choice between whole rows and column slabs lies in the chunk's first
+  // output element, which the W product behind it overwrites (so it needs no room in
+  // the workspace); not when the output lies over the self rows that W reads.
+  const uintptr_t in0 = reinterpret_cast<uintptr_t>(h_in), out0 = reinterpret_cast<uintptr_t>(h_out);
+  const bool apart = in0 + (size_t)n_in * L->d_in * es <= out0 ||
+                     out0 + (size_t)n_out * L->d_out * es <= in0;
+  const bool slabs = !short_rows && apart && out0 % 4 == 0 &&
+                     pool_slabs_wanted(n_transform, (int64_t)pool_width * es, n_out);
   for (int64_t r0 = 0; r0 < n_out; r0 += kChunkRows) {
     const int64_t rows = (n_out - r0) < kChunkRows ? (n_out - r0) : kChunkRows;
     const int T = nbr->top_t;
+    unsigned char* const out_rows = static_cast<unsigned char*>(h_out) + (size_t)r0 * L->d_out * es;
     PoolLaunch pl{};
     pl.P = table;
     pl.n_transform = n_transform;
@@ -443,7 +448,7 @@ int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
     pl.rows = rows;
     pl.out = nbuf;
     pl.mode = (int)L->pool;
-    if (lw.choice && !short_rows) pl.slabbed = reinterpret_cast<int*>(table + lw.choice_at());
+    if (slabs) pl.slabbed = reinterpret_cast<int*>(out_rows);
     e = launch_pool(pl, s);
     if (e != hipSuccess) return hip_fail(e, "pool launch");
 
@@ -472,7 +477,7 @@ int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
     gw.bias = L->w;
     gw.M = rows;
     gw.N = L->d_out;
-    gw.C = static_cast<unsigned char*>(h_out) + (size_t)r0 * L->d_out * es;
+    gw.C = out_rows;
     gw.bf16 = bf16;
     gw.relu = true;
     gw.l2norm = true;

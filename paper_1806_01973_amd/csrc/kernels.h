@@ -129,6 +129,7 @@ struct PoolLaunch {
   int mode;  // PoolMode
   // Device int for the launch's choice between whole rows and column slabs, or
   // null (whole rows); give one when pool_slabs_wanted and the rows may be deep.
+  // Free again when the launch's kernels end.
   int* slabbed = nullptr;
 };
 bool pool_slabs_wanted(int64_t n_transform, int64_t row_bytes, int64_t rows);

@@ -20,8 +20,9 @@ def _run(dt, n, m, T, rows, pool, weights, short, popular, seed=1):
     g = torch.Generator(device="cuda").manual_seed(seed)
     eye = torch.eye(m, device="cuda")
     # P = ReLU(h I + 0) = h for h >= 0; W's self half is zero.
-    layer = ps.DeviceLayer(eye, torch.zeros(m), torch.cat([torch.zeros((m, m), device="cuda"), eye], 1),
-                           torch.zeros(m), dtype=dt, pool=pool)
+    dout = min(m, 512)  # the widest output; the last columns of wider rows
+    W = torch.cat([torch.zeros((dout, m), device="cuda"), eye[m - dout:]], 1)
+    layer = ps.DeviceLayer(eye, torch.zeros(m), W, torch.zeros(dout), dtype=dt, pool=pool)
     h = torch.rand((n, m), generator=g, device="cuda").to(dt)
     nbr = ps.Neighborhoods.empty(rows, T, weights)
     idx = torch.randint(0, n, (rows, T), generator=g, device="cuda")
@@ -52,12 +53,14 @@ def _run(dt, n, m, T, rows, pool, weights, short, popular, seed=1):
     else:
         a = w[pick].double() if pool == "importance" else ok / ok.sum(1, keepdim=True).clamp(min=1).double()
         z = (x * torch.where(ok, a, 0.0)[..., None]).sum(1)
+    z = z[:, m - dout:]
     norm = z.norm(dim=1, keepdim=True)
     ref = torch.where(norm > 0, z / norm, 0.0)
     tol = ref * 2 * (T + m ** 0.5 + 8) * 2.0 ** -24
     if dt == torch.bfloat16:
         tol = tol + ref * 2 * 2.0 ** -8
     assert ((out[pick].double() - ref).abs() <= tol).all()
+    return layer, h, nbr, out
 
 
 @pytest.mark.parametrize("pool", ["importance", "mean", "max"])
@@ -75,3 +78,15 @@ def test_slabs_and_whole_rows(pool, dt, n, m, T, weights, short, popular):
     print(f"[case] pool slabs {pool} {dt} n={n} m={m} T={T} short={short} popular={popular}",
           flush=True)
     _run(dt, n, m, T, 16_384 + 77, pool, weights, short, popular)
+
+
+def test_the_choice_does_not_depend_on_the_workspace():
+    """A workspace with no room for the split weights gives the same bits, slabs or not."""
+    import paper_1806_01973_amd as ps
+    n, m, T, rows = 60_000, 256, 64, 140_001
+    layer, h, nbr, out = _run(torch.float32, n, m, T, rows, "importance", True, False, True)
+    rows_of = lambda r: (r * m * 4 + 255) // 256 * 256
+    small = torch.empty(rows_of(n) + rows_of(rows), dtype=torch.uint8, device="cuda")
+    assert small.numel() < ps.convolve_workspace_size(layer, n, rows)
+    self_rows = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    assert torch.equal(ps.convolve_layer(layer, h, n, nbr, self_rows=self_rows, workspace=small), out)
