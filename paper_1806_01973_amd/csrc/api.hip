@@ -431,7 +431,7 @@ int run_pool_dense(const pinsage_layer_t* L, const void* h_in, int64_t n_in,
   const bool apart = in0 + (size_t)n_in * L->d_in * es <= out0 ||
                      out0 + (size_t)n_out * L->d_out * es <= in0;
   const bool slabs = !short_rows && apart && out0 % 4 == 0 &&
-                     pool_slabs_wanted(n_transform, (int64_t)pool_width * es, n_out);
+                     pool_slabs_wanted(n_transform, (int64_t)pool_width * es, n_out, nbr->top_t);
   for (int64_t r0 = 0; r0 < n_out; r0 += kChunkRows) {
     const int64_t rows = (n_out - r0) < kChunkRows ? (n_out - r0) : kChunkRows;
     const int T = nbr->top_t;

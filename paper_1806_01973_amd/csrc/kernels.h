@@ -132,7 +132,7 @@ struct PoolLaunch {
   // Free again when the launch's kernels end.
   int* slabbed = nullptr;
 };
-bool pool_slabs_wanted(int64_t n_transform, int64_t row_bytes, int64_t rows);
+bool pool_slabs_wanted(int64_t n_transform, int64_t row_bytes, int64_t rows, int T);
 hipError_t launch_pool(const PoolLaunch& a, hipStream_t s);
 
 // Pool and W fused (poolw.hip): out[r] = L2norm(ReLU(W_s h[self(r)] + pool(R, N(r))

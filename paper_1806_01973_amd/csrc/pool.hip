@@ -355,42 +355,64 @@ __global__ __launch_bounds__(256) void pool_head_kernel(PoolLaunch a) {
 
 // Decides between whole rows and column slabs (below) from kProbes sampled slots:
 // slabs pay when the neighbourhoods are deep (a header is read per slab) and when
-// some rows are gathered far more often than others, so that the slices of the
-// popular ones stay in the L2s. The sample's pairs of equal ids estimate the sum
-// of squared gather frequencies; 12 pairs among 2,048 samples is 6e-6, as when the
-// 32K rows whose 128-byte slices fill one XCD's L2 take 44% of the gathers.
-constexpr int kProbes = 2048;
+// enough gathers go to rows that are gathered again and again, so that their slices
+// stay in the L2s: the share of samples whose id was sampled more than once. Slabs
+// against whole rows at T = 50, by that share: tables beyond the last-level cache, 700K
+// rows of 1 KB in fp32 0.03 1.07x the time, 0.07 1.04, 0.11 1.01, 0.19 0.97, 0.23 0.93,
+// 0.50 0.82, in bf16 1.12, 1.08, 1.05, 1.00, 0.98 and 0.88; 1.5M 1.02 at 0.07 and 0.97
+// at 0.18; the 1.2M-node graph's pins 0.79 at 0.19. Tables inside it, 200K rows of 1 KB
+// 0.99 at 0.05 and 0.86 at 0.32, 100K of 2 KB 0.89 at 0.10. (The pairs of equal ids
+// among 2,048 samples, tried before, do not tell a few very popular rows from many
+// popular ones: 77 at 1.08x, 64 at 0.79x.)
+constexpr int kProbes = 8192;
 __global__ __launch_bounds__(1024) void pool_probe_kernel(PoolLaunch a, int min_live) {
   constexpr int kSlots = 2 * kProbes;
+  constexpr int kEach = kProbes / 1024;
   __shared__ uint32_t keys[kSlots], seen[kSlots];
-  __shared__ int live, pairs;
+  __shared__ int live, repeated;
   for (int i = threadIdx.x; i < kSlots; i += 1024) {
     keys[i] = 0xFFFFFFFFu;
     seen[i] = 0u;
   }
-  if (threadIdx.x == 0) live = pairs = 0;
-  __syncthreads();
-  for (int i = threadIdx.x; i < kProbes; i += 1024) {
-    const uint32_t x = (uint32_t)i * 0x9E3779B9u;
+  if (threadIdx.x == 0) live = repeated = 0;
+  int32_t ids[kEach];
+#pragma unroll
+  for (int e = 0; e < kEach; ++e) {
+    const uint32_t x = (uint32_t)(e * 1024 + (int)threadIdx.x) * 0x9E3779B9u;
     const int64_t row = (int64_t)(((uint64_t)x * (uint64_t)a.rows) >> 32);
     const int t = (int)(((uint64_t)(x * 0x85EBCA6Bu) * (uint64_t)a.T) >> 32);
-    const int32_t v = a.idx[row * a.T + t];
-    if ((uint64_t)(int64_t)v >= (uint64_t)a.n_transform) continue;
-    atomicAdd(&live, 1);
-    uint32_t h = ((uint32_t)v * 0x9E3779B9u) >> (32 - 12);
-    static_assert(kSlots == 1 << 12, "home slot");
+    ids[e] = a.idx[row * a.T + t];
+  }
+  __syncthreads();
+  int n = 0;
+#pragma unroll
+  for (int e = 0; e < kEach; ++e) {
+    const uint32_t v = (uint32_t)ids[e];
+    if ((uint64_t)(int64_t)ids[e] >= (uint64_t)a.n_transform) continue;
+    ++n;
+    uint32_t h = (v * 0x9E3779B9u) >> (32 - 14);
+    static_assert(kSlots == 1 << 14, "home slot");
     for (;;) {  // half full at most, so a free slot is found
-      const uint32_t k = atomicCAS(&keys[h], 0xFFFFFFFFu, (uint32_t)v);
-      if (k == 0xFFFFFFFFu || k == (uint32_t)v) break;
+      const uint32_t k = atomicCAS(&keys[h], 0xFFFFFFFFu, v);
+      if (k == 0xFFFFFFFFu || k == v) break;
       h = (h + 1) & (kSlots - 1);
     }
-    atomicAdd(&pairs, (int)atomicAdd(&seen[h], 1u));
+    atomicAdd(&seen[h], 1u);
+  }
+  __syncthreads();
+  int again = 0;
+  for (int i = threadIdx.x; i < kSlots; i += 1024) again += seen[i] > 1u ? (int)seen[i] : 0;
+  n = wave_sum_i32(n);
+  again = wave_sum_i32(again);
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(&live, n);
+    atomicAdd(&repeated, again);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const int64_t n = live;
-    *a.slabbed = n * a.T >= (int64_t)min_live * kProbes &&
-                 (int64_t)pairs * kProbes * kProbes >= 12 * n * n;
+    const int64_t table = a.n_transform * (int64_t)a.m * (a.bf16 ? 2 : 4);
+    const int least = table <= (256ll << 20) ? 5 : 12;  // percent
+    *a.slabbed = (int64_t)live * a.T >= (int64_t)min_live * kProbes && repeated * 100 >= live * least;
   }
 }
 
@@ -406,7 +428,7 @@ __global__ __launch_bounds__(1024) void pool_probe_kernel(PoolLaunch a, int min_
 // are added by halving (each step exchanges half of the values a lane still
 // holds), in the same tree as a butterfly. pool_probe_kernel decides; this kernel
 // and pool_kernel (whole rows, launched behind it) each end at once if not chosen
-// (with the probe about 20 us where whole rows are).
+// (with the probe 10 to 30 us where whole rows are).
 // What bounds it: cache bandwidth, about 13 TB/s of gathered bytes, and at 128
 // bytes an item the issue slots. T = 50, pin degree Zipf(2): 1M rows of 1 KB
 // (fp32) 6.60 -> 5.19 ms; 300K of 1 KB (bf16) 1.72 -> 1.36; 100K of 2 KB, max
@@ -588,7 +610,10 @@ hipError_t launch_mode(PoolLaunch a, hipStream_t s) {
   if (const int bytes = slab_bytes(a)) {
     const hipError_t e = launch_slabs<BF16, MODE>(a, bytes, s);
     if (e != hipSuccess) return e;
-    cap = 1ll << 15;  // whole rows behind it, in fewer blocks to end
+    // Whole rows behind it. Ending 2^18 blocks takes up to 50 us of a pool in slabs
+    // (1.2M rows of 1 KB, T = 50: 5.06 -> 5.11 ms); in 2^15 blocks whole rows that were
+    // chosen take 4% longer (9.51 -> 9.89 ms, evenly spread).
+    cap = 1ll << 18;
   } else {
     a.slabbed = nullptr;
   }
@@ -641,11 +666,13 @@ hipError_t launch_typed(const PoolLaunch& a, hipStream_t s) {
 
 }  // namespace
 
-// Tables the slabs are for: rows of 1 KB and more, 48 MB and more (byte offsets
-// are 32 bits), enough rows for the probe's launch not to matter.
-bool pool_slabs_wanted(int64_t n_transform, int64_t row_bytes, int64_t rows) {
+// Pools the slabs are for: tables of rows of 1 KB and more, 48 MB and more (byte
+// offsets are 32 bits), and 8 GB or more to gather (about 1.2 ms), beside which the
+// probe and the empty launch, 10 to 20 us, count little.
+bool pool_slabs_wanted(int64_t n_transform, int64_t row_bytes, int64_t rows, int T) {
   const int64_t table = n_transform * row_bytes;
-  return row_bytes >= 1024 && rows >= 16384 && table >= (48ll << 20) && table < (1ll << 32) - 16;
+  return row_bytes >= 1024 && table >= (48ll << 20) && table < (1ll << 32) - 16 &&
+         rows * row_bytes * T >= (8ll << 30);
 }
 
 hipError_t launch_pool(const PoolLaunch& a, hipStream_t s) {

@@ -1,5 +1,5 @@
-"""The pool over column slabs (tables of 48 MB and more, rows of 1 KB and more, deep
-neighbourhoods that share popular rows) and its turn to whole rows where the probe finds
+"""The pool over column slabs (tables of 48 MB and more, rows of 1 KB and more, 8 GB of
+them gathered, deep neighbourhoods that share popular rows) and its turn to whole rows where the probe finds
 them short or evenly spread, in layers whose W passes the pooled
 rows through: W = [0 | I], so the layer's output is the pooled row, ReLU'd and normalised.
 
@@ -78,6 +78,37 @@ def test_slabs_and_whole_rows(pool, dt, n, m, T, weights, short, popular):
     print(f"[case] pool slabs {pool} {dt} n={n} m={m} T={T} short={short} popular={popular}",
           flush=True)
     _run(dt, n, m, T, 16_384 + 77, pool, weights, short, popular)
+
+
+# At 8 GB of gathered rows and more the probe runs and the choice shows: a call with few
+# of the same rows always takes whole rows, whose sums have another order (an element in
+# a few hundred thousand then rounds otherwise at the least, also in bf16).
+@pytest.mark.parametrize("pool", ["importance", "mean", "max"])
+@pytest.mark.parametrize("dt,n,m,T,rows,weights,short,popular,slabs", [
+    (torch.float32, 50_003, 256, 50, 175_003, True, False, True, True),     # 256-byte slabs
+    (torch.float32, 60_000, 272, 64, 140_001, False, False, True, True),    # last slab not whole
+    (torch.float32, 530_001, 256, 64, 140_001, True, False, True, True),    # 128-byte slabs
+    (torch.bfloat16, 60_000, 512, 64, 140_001, True, False, True, True),    # 256-byte slabs
+    (torch.bfloat16, 60_000, 528, 62, 140_001, False, False, True, True),   # last slab not whole
+    (torch.bfloat16, 530_000, 528, 64, 140_001, True, False, True, True),   # 128-byte slabs
+    (torch.float32, 530_000, 256, 64, 140_001, True, False, False, False),  # evenly spread
+    (torch.float32, 60_000, 256, 64, 140_001, True, True, True, False),     # short rows
+    (torch.bfloat16, 60_000, 512, 64, 140_001, False, True, True, False),
+])
+def test_the_choice_between_slabs_and_whole_rows(pool, dt, n, m, T, rows, weights, short, popular,
+                                                 slabs):
+    import paper_1806_01973_amd as ps
+    print(f"[case] pool choice {pool} {dt} n={n} m={m} T={T} short={short} popular={popular}",
+          flush=True)
+    layer, h, nbr, out = _run(dt, n, m, T, rows, pool, weights, short, popular)
+    k = 100_000
+    part = ps.Neighborhoods(nbr.idx[:k], nbr.counts[:k], nbr.weights[:k] if weights else None)
+    self_rows = torch.zeros(k, dtype=torch.int32, device="cuda")
+    whole = ps.convolve_layer(layer, h, n, part, self_rows=self_rows)
+    if pool == "max":  # the same bits either way
+        assert torch.equal(whole, out[:k])
+    else:
+        assert torch.equal(whole, out[:k]) != slabs
 
 
 def test_the_choice_does_not_depend_on_the_workspace():
