@@ -54,9 +54,9 @@
 // Epilogue: + bias, + an optional addend matrix (the pooled neighbour term
 // when W is split, see run_layer), ReLU (optional without L2), store in the
 // storage dtype; with L2 the block spans
-// all N columns, and a row's sum of squares is added over the lane's own
-// columns, its partner half-wave and then the waves of the row band in a fixed
-// order through LDS; every row is scaled by 1/||z|| (zero rows stay zero).
+// all N columns, and a row's sum of squares is added over every 32 columns (a
+// lane's 16 and its partner half-wave's) and then over those sums in order,
+// through LDS; every row is scaled by 1/||z|| (zero rows stay zero).
 //
 // Tile order is XCD-aware: hardware hands block b to XCD b % 8; blocks are
 // renumbered so that each XCD gets a contiguous run of tiles, keeping the
@@ -112,7 +112,7 @@ struct Cfg {
   static constexpr int ROW_DPW = PRE ? A_GROUPS / NWAVES : DPW;  // of them, row groups
   static constexpr int PENDING = (STAGES - 2) * DPW;
   static constexpr int STAGE_BYTES = GROUPS * kGroupBytes;
-  static constexpr int RED_BYTES = L2 ? WAVES_N * BM * 4 : 0;
+  static constexpr int RED_BYTES = L2 ? BN / 32 * BM * 4 : 0;  // a sum per row and 32 columns
   static constexpr int BIAS_BYTES = BN * 4;
   static constexpr int FLAG_BYTES = BF16 ? 0 : 16;  // fp32: some wave's results need a redo
   static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + RED_BYTES + BIAS_BYTES + FLAG_BYTES;
@@ -238,11 +238,16 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   // The large bf16 tiles start their K sweep at different chunks (rotation by
   // the tile's index in the whole product): rows of A and B sit at power-of-two
   // strides, and blocks that all read the same K columns at once would pile onto
-  // a few L2 channels. The others (where it measured neutral) sum K in order, so
-  // that a row's bits do not depend on the tile shape its launch takes.
-  constexpr bool kRotate = C::kBf16 && BM * BN >= 128 * 256;
-  const int kshift =
-      kRotate ? (int)((tile + (a.row_base / BM) * tiles_n) % nchunks) : 0;
+  // a few L2 channels. Smaller tiles of the same product (few rows) rotate as the
+  // large tile around them would, so that a row's bits do not depend on the tile
+  // shape its launch takes; products whose large tiles are fp32, or narrow, or
+  // gemm_rs_kernel's sum K in order (where it measured neutral).
+  int kshift = 0;
+  if constexpr (C::kBf16) {
+    if (a.rot_m)
+      kshift = (int)(((a.row_base + m0) / a.rot_m * ((a.N + a.rot_n - 1) / a.rot_n) + n0 / a.rot_n) %
+                     nchunks);
+  }
   // Issues the DMAs of the chunk-th chunk of this tile's sweep into its
   // stage. Sweep positions past the end read the zero row, which keeps the
   // in-flight count uniform for wait_vmcnt.
@@ -603,6 +608,7 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   // whole. (Loading the addend tile the same way, in
   // front of the epilogue, measured slower: its latency is then exposed.)
   constexpr int TROW = BN * ESZ + 16;
+  constexpr int NORM_SUMS = BN / 32;  // per row, side by side
   constexpr bool kStaged = C::kBf16 && BM * TROW <= STAGES * C::STAGE_BYTES;
   constexpr int PER_ROW = BN / VEC;  // 16-byte pieces per tile row
   // + bias (+ addend), then ReLU unless disabled; the L2 epilogue always
@@ -632,11 +638,14 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
     }
   };
   // acc[i] = its band + bias + addend (lane_row: the addend's row of this
-  // lane, shifted to column 0 of the tile; null = none), ReLU; returns the lane's sum of squares.
+  // lane, shifted to column 0 of the tile; null = none), ReLU. For the row norm also the
+  // sum of squares of every 32 columns, the lane's and its partner half-wave's
+  // (lane ^ 32), into LDS.
   auto finish_band = [&](int i, const unsigned char* lane_row) __attribute__((always_inline)) {
-    float s = 0.0f;
+    float sum[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TN; ++j) {
+      float s = 0.0f;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const float4 bv = *reinterpret_cast<const float4*>(bias_s + c0(j, g));
@@ -650,7 +659,16 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
           s = fmaf(y, y, s);
         }
       }
-    return s;
+      sum[j] = s;
+    }
+    if constexpr (C::L2) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) sum[j] += __shfl_xor(sum[j], 32);
+      if (half == 0)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          red[(a_base_row + i * 32 + row_in_blk) * NORM_SUMS + wn * TN + j] = sum[j];
+    }
   };
   auto stage_band = [&](int i, unsigned char* lane_row, float scale)
       __attribute__((always_inline)) {
@@ -680,26 +698,18 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
                ? static_cast<const unsigned char*>(a.addend) + (r * a.N + n0) * ESZ
                : nullptr;
   };
-  // Row norm: the lane's columns, its partner half-wave (lane ^ 32), then the
-  // WAVES_N waves of the row band in a fixed order through LDS.
-  auto put_partial = [&](int i, float s) __attribute__((always_inline)) {
-    s += __shfl_xor(s, 32);
-    if (half == 0) red[wn * BM + a_base_row + i * 32 + row_in_blk] = s;
-  };
+  // Row norm: the 32-column sums of the row in order, whatever the tile shape.
   auto row_scale = [&](int i) __attribute__((always_inline)) {
     const int r = a_base_row + i * 32 + row_in_blk;
     float ss = 0.0f;
 #pragma unroll
-    for (int w = 0; w < C::WAVES_N; ++w) ss += red[w * BM + r];
+    for (int w = 0; w < NORM_SUMS; ++w) ss += red[r * NORM_SUMS + w];
     return ss > 0.0f ? 1.0f / sqrtf(ss) : 0.0f;
   };
 
   if constexpr (kStaged) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const float s = finish_band(i, addend_row(i));
-      if constexpr (C::L2) put_partial(i, s);
-    }
+    for (int i = 0; i < TM; ++i) finish_band(i, addend_row(i));
     if constexpr (C::L2) __syncthreads();
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -735,7 +745,7 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
           }
           __syncthreads();
         }
-        put_partial(i, finish_band(i, a.addend ? lane_row : nullptr));
+        finish_band(i, a.addend ? lane_row : nullptr);
         __syncthreads();  // partial sums visible; every addend read of the band done
         stage_band(i, lane_row, row_scale(i));
       } else {
@@ -1181,10 +1191,15 @@ size_t split_b_bytes(int N, int K) {
   return (size_t)(K / 16) * blocks * 3072 + blocks * 4;
 }
 
-hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s) {
+hipError_t launch_gemm(GemmLaunch a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   ProfileScope prof(a.prof_class >= 0 ? a.prof_class : (a.l2norm ? kKGemmW : (a.relu ? kKGemmQ : kKGemmR)), s);
   if (a.l2norm && a.N > 512) return hipErrorInvalidValue;
+  // The tile that the K rotation follows: the large one's, whichever runs.
+  if (a.bf16 && (a.l2norm ? a.N > 128 : !use_rs(a))) {
+    a.rot_m = a.l2norm ? 128 : 256;
+    a.rot_n = a.l2norm && a.N > 256 ? 512 : 256;
+  }
   hipError_t few = hipSuccess;
   if (launch_few(a, s, &few)) return few;
   if (use_rs(a)) return launch_rs(a, s);

@@ -53,3 +53,35 @@ def test_row_norm_layers_of_few_rows(dtype, rows, d, m, dout):
     if dtype == "bf16":
         tol = tol + ref * 2.0 ** -8
     assert ((out - ref).abs() <= tol).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dataflow", ["pool_then_dense", "dense_then_pool"])
+@pytest.mark.parametrize("d,m,dout", [(64, 48, 64), (96, 64, 128), (288, 336, 176), (160, 512, 256),
+                                      (256, 64, 512)])
+def test_layer_row_bits_do_not_depend_on_the_row_count(dtype, dataflow, d, m, dout):
+    """A layer's rows, behind row maps on both sides and with one neighbour each, have the
+    same bits whatever the number of rows beside them: transform, neighbour half and
+    row-norm product change tile shapes in between (8,192, 16,384 and 32,768 rows, and
+    below one large tile per CU), and with them the K sweep's start in bf16."""
+    import paper_1806_01973_amd as ps
+    print(f"[case] layer row bits {dtype} {dataflow} {d}/{m}/{dout}", flush=True)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(d + m)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
+    layer = ps.DeviceLayer(rnd(m, d) * d ** -0.5, rnd(m) * 0.1, rnd(dout, d + m) * (d + m) ** -0.5,
+                           rnd(dout) * 0.1, dtype=dt, dataflow=dataflow)
+    N = 70_001
+    h = rnd(N, d).to(dt)
+    nbr = ps.Neighborhoods.empty(N, 1)
+    nbr.idx.copy_(torch.arange(N)[:, None])
+    nbr.counts.fill_(1), nbr.weights.fill_(1.0)
+    maps = [torch.randperm(N, generator=g, device="cuda").to(torch.int32) for _ in range(2)]
+
+    def rows(k):
+        part = ps.Neighborhoods(nbr.idx[:k], nbr.counts[:k], nbr.weights[:k])
+        return ps.convolve_layer(layer, h, k, part, self_rows=maps[0][:k], transform_rows=maps[1][:k])
+
+    full = rows(N)
+    for k in (1, 500, 8192, 8193, 12_788, 16_384, 16_385, 32_000, 33_000, 60_000):
+        assert torch.equal(rows(k), full[:k]), k
