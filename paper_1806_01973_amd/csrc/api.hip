@@ -134,14 +134,19 @@ int check_mlp(const pinsage_mlp_t* M) {
   return PINSAGE_OK;
 }
 
-// Products of at least this many rows take their fp32 weights split once
-// (split_b_bytes of workspace each) rather than in every tile: 1.2M x 256 ->
-// 256 takes 1.01 ms instead of 1.11. At 16K rows (about 25 us) the saving and the
-// split's own launch (about 5 us) are equal. A workspace without room for the split weights is accepted all the
-// same; the tiles then split them, to the same bits.
+// fp32 products of more than 16,384 rows and 3 G multiply-adds take their weights split
+// once (split_b_bytes of workspace each) rather than in every tile. At 16,384 rows all
+// tiles that split them run at once, one 64-row row-norm tile per CU: 256 outputs, K =
+// 768, 52.8 us against 74.6 with split weights and 128-row tiles. From there on, split in
+// the tiles / before: 256 outputs, K = 768, 20,000 rows (3.9 G) 80 / 76 us; 128, K = 256,
+// 20,000 (0.7 G) 23.1 / 26.7 and 1M (33 G) 517 / 487; 128, K = 1,024, 20,000 (2.6 G) 62.6 /
+// 67.6 and 200,000 410 / 388; 64, K = 64 never (1M rows 131 / 154). A workspace without
+// room for the split weights is accepted all the same; the tiles then split them, to the
+// same bits.
 constexpr int64_t kSplitRows = 1ll << 14;
 inline size_t split_ws(pinsage_dtype_t dtype, int64_t rows, int n, int k) {
-  return dtype == PINSAGE_F32 && rows >= kSplitRows ? align_up(split_b_bytes(n, k)) : 0;
+  const bool worth = rows > kSplitRows && k >= 128 && rows * n >= (3ll << 30) / k;
+  return dtype == PINSAGE_F32 && worth ? align_up(split_b_bytes(n, k)) : 0;
 }
 
 // Hidden rows | split G1 | split G2 (the last two when `pre`).
@@ -159,6 +164,7 @@ int run_mlp(const pinsage_mlp_t* M, const void* h, const int32_t* rowmap, int64_
   const size_t es = elem_size(M->dtype);
   const bool bf16 = M->dtype == PINSAGE_BF16;
   const size_t s1 = pre ? split_ws(M->dtype, n, M->d_hidden, M->d_in) : 0;
+  const size_t s2 = pre ? split_ws(M->dtype, n, M->d_out, M->d_hidden) : 0;
   unsigned char* const split1 = static_cast<unsigned char*>(ws) + mlp_ws(M, n, false);
   for (int64_t r0 = 0; r0 < n; r0 += kChunkRows) {
     const int64_t rows = (n - r0) < kChunkRows ? (n - r0) : kChunkRows;
@@ -195,7 +201,7 @@ int run_mlp(const pinsage_mlp_t* M, const void* h, const int32_t* rowmap, int64_
     g2.C = static_cast<unsigned char*>(z) + (size_t)r0 * M->d_out * es;
     g2.bf16 = bf16;
     g2.prof_class = kKMlp;
-    if (s1) g2.Bs = split1 + s1;
+    if (s2) g2.Bs = split1 + s1;
     e = launch_gemm(g2, s);
     if (e != hipSuccess) return hip_fail(e, "output layer G2 launch");
   }

@@ -54,9 +54,9 @@
 // Epilogue: + bias, + an optional addend matrix (the pooled neighbour term
 // when W is split, see run_layer), ReLU (optional without L2), store in the
 // storage dtype; with L2 the block spans
-// all N columns, and a row's sum of squares is added over every 32 columns (a
-// lane's 16 and its partner half-wave's) and then over those sums in order,
-// through LDS; every row is scaled by 1/||z|| (zero rows stay zero).
+// all N columns, and a row's sum of squares is added over a lane's own columns, its
+// partner half-wave and then the groups of 64 (bf16 512 outputs: 128) columns in
+// order, through LDS; every row is scaled by 1/||z|| (zero rows stay zero).
 //
 // Tile order is XCD-aware: hardware hands block b to XCD b % 8; blocks are
 // renumbered so that each XCD gets a contiguous run of tiles, keeping the
@@ -84,8 +84,9 @@ constexpr int kGroupBytes = 1024;    // 16 rows x 64 bytes: one DMA instruction
 __device__ __forceinline__ int vec_slot(int r, int v) { return v ^ (((r >> 1) ^ (r >> 3)) & 3); }
 
 template <bool BF16, int BM_, int BN_, int WAVES_M_, int WAVES_N_, bool L2_, int STAGES_,
-          int WPE_ = 1, bool PRE_ = false>
+          int WPE_ = 1, bool PRE_ = false, bool ROT_ = false>
 struct Cfg {
+  static constexpr bool ROT = ROT_;  // bf16: the K sweep starts where the product's large tile does
   static constexpr bool PRE = PRE_;  // fp32: B arrives split (launch_split_b)
   static constexpr int WPE = WPE_;  // waves per SIMD the register budget must allow
   static constexpr bool kBf16 = BF16;
@@ -112,7 +113,13 @@ struct Cfg {
   static constexpr int ROW_DPW = PRE ? A_GROUPS / NWAVES : DPW;  // of them, row groups
   static constexpr int PENDING = (STAGES - 2) * DPW;
   static constexpr int STAGE_BYTES = GROUPS * kGroupBytes;
-  static constexpr int RED_BYTES = L2 ? BN / 32 * BM * 4 : 0;  // a sum per row and 32 columns
+  // Sums of squares of a row: per group of 32-column blocks (a wave's of the large
+  // shapes), or per block and half-wave where a wave holds less than a group.
+  static constexpr int NORM_GROUP = BF16 && BN > 256 ? 4 : 2;
+  static constexpr bool NORM_WHOLE = TN == NORM_GROUP;
+  static constexpr int NORM_SUMS = NORM_WHOLE ? WAVES_N : BN / 16;
+  static_assert(!L2_ || NORM_GROUP % TN == 0, "a wave holds a group or a part of one");
+  static constexpr int RED_BYTES = L2 ? NORM_SUMS * BM * 4 : 0;
   static constexpr int BIAS_BYTES = BN * 4;
   static constexpr int FLAG_BYTES = BF16 ? 0 : 16;  // fp32: some wave's results need a redo
   static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + RED_BYTES + BIAS_BYTES + FLAG_BYTES;
@@ -243,10 +250,9 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   // shape its launch takes; products whose large tiles are fp32, or narrow, or
   // gemm_rs_kernel's sum K in order (where it measured neutral).
   int kshift = 0;
-  if constexpr (C::kBf16) {
-    if (a.rot_m)
-      kshift = (int)(((a.row_base + m0) / a.rot_m * ((a.N + a.rot_n - 1) / a.rot_n) + n0 / a.rot_n) %
-                     nchunks);
+  if constexpr (C::ROT) {  // large tiles: 128 rows by all columns (row norm), 256 x 256
+    const uint32_t tm = (uint32_t)((a.row_base + m0) >> (C::L2 ? 7 : 8));
+    kshift = (int)((C::L2 ? tm : tm * (uint32_t)((a.N + 255) >> 8) + (n0 >> 8)) % (uint32_t)nchunks);
   }
   // Issues the DMAs of the chunk-th chunk of this tile's sweep into its
   // stage. Sweep positions past the end read the zero row, which keeps the
@@ -608,7 +614,7 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   // whole. (Loading the addend tile the same way, in
   // front of the epilogue, measured slower: its latency is then exposed.)
   constexpr int TROW = BN * ESZ + 16;
-  constexpr int NORM_SUMS = BN / 32;  // per row, side by side
+  constexpr int NORM_SUMS = C::NORM_SUMS;  // per row, side by side
   constexpr bool kStaged = C::kBf16 && BM * TROW <= STAGES * C::STAGE_BYTES;
   constexpr int PER_ROW = BN / VEC;  // 16-byte pieces per tile row
   // + bias (+ addend), then ReLU unless disabled; the L2 epilogue always
@@ -639,8 +645,8 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
   };
   // acc[i] = its band + bias + addend (lane_row: the addend's row of this
   // lane, shifted to column 0 of the tile; null = none), ReLU. For the row norm also the
-  // sum of squares of every 32 columns, the lane's and its partner half-wave's
-  // (lane ^ 32), into LDS.
+  // sums of squares into LDS: each block's columns of this lane, blocks in order, then the
+  // partner half-wave's (lane ^ 32); a wave with less than a group leaves all apart.
   auto finish_band = [&](int i, const unsigned char* lane_row) __attribute__((always_inline)) {
     float sum[TN];
 #pragma unroll
@@ -662,12 +668,16 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
       sum[j] = s;
     }
     if constexpr (C::L2) {
+      float* const row_sums = red + (a_base_row + i * 32 + row_in_blk) * NORM_SUMS;
+      if constexpr (!C::NORM_WHOLE) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) sum[j] += __shfl_xor(sum[j], 32);
-      if (half == 0)
+        for (int j = 0; j < TN; ++j) row_sums[2 * (wn * TN + j) + half] = sum[j];
+      } else {
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          red[(a_base_row + i * 32 + row_in_blk) * NORM_SUMS + wn * TN + j] = sum[j];
+        for (int j = 1; j < TN; ++j) sum[0] += sum[j];
+        sum[0] += __shfl_xor(sum[0], 32);
+        if (half == 0) row_sums[wn] = sum[0];
+      }
     }
   };
   auto stage_band = [&](int i, unsigned char* lane_row, float scale)
@@ -698,12 +708,25 @@ __global__ __launch_bounds__(C::THREADS, C::WPE) void gemm_kernel(GemmLaunch a) 
                ? static_cast<const unsigned char*>(a.addend) + (r * a.N + n0) * ESZ
                : nullptr;
   };
-  // Row norm: the 32-column sums of the row in order, whatever the tile shape.
+  // Row norm: the groups' sums of the row in order, the same whatever the tile shape.
   auto row_scale = [&](int i) __attribute__((always_inline)) {
     const int r = a_base_row + i * 32 + row_in_blk;
     float ss = 0.0f;
 #pragma unroll
-    for (int w = 0; w < NORM_SUMS; ++w) ss += red[r * NORM_SUMS + w];
+    for (int w = 0; w < BN / 32 / C::NORM_GROUP; ++w) {
+      if constexpr (!C::NORM_WHOLE) {
+        const float* const g = red + r * NORM_SUMS + w * 2 * C::NORM_GROUP;
+        float lo = g[0], hi = g[1];
+#pragma unroll
+        for (int j = 1; j < C::NORM_GROUP; ++j) {
+          lo += g[2 * j];
+          hi += g[2 * j + 1];
+        }
+        ss += lo + hi;
+      } else {
+        ss += red[r * NORM_SUMS + w];
+      }
+    }
     return ss > 0.0f ? 1.0f / sqrtf(ss) : 0.0f;
   };
 
@@ -1107,28 +1130,43 @@ hipError_t launch_cfg(const GemmLaunch& a, hipStream_t s) {
 }
 
 #ifndef PINSAGE_CFG_Q_BF16
-#define PINSAGE_CFG_Q_BF16 Cfg<true, 256, 256, 2, 2, false, 4>
+#define PINSAGE_CFG_Q_BF16 Cfg<true, 256, 256, 2, 2, false, 4, 1, false, true>
 #endif
 #ifndef PINSAGE_CFG_Q_F32
 #define PINSAGE_CFG_Q_F32 Cfg<false, 128, 128, 2, 2, false, PRE ? 3 : 4, 2, PRE>
 #endif
 #ifndef PINSAGE_CFG_W256_BF16
-#define PINSAGE_CFG_W256_BF16 Cfg<true, 128, 256, 2, 4, true, 3>
+#define PINSAGE_CFG_W256_BF16 Cfg<true, 128, 256, 2, 4, true, 3, 1, false, true>
 #endif
 #ifndef PINSAGE_CFG_W256_F32
 #define PINSAGE_CFG_W256_F32 Cfg<false, PRE ? 128 : 64, 256, PRE ? 2 : 1, 4, true, 3, 2, PRE>
 #endif
 #ifndef PINSAGE_CFG_W512_BF16
-#define PINSAGE_CFG_W512_BF16 Cfg<true, 128, 512, 2, 4, true, 3>
+#define PINSAGE_CFG_W512_BF16 Cfg<true, 128, 512, 2, 4, true, 3, 1, false, true>
 #endif
 
-// Tile shapes by dtype, epilogue, output width and how many tiles there are.
-// Below one large tile per CU (256) the chip is better filled by small ones: a
-// 2,500-row layer has 16 tiles of 128 x 128 but 32 of 64 x 64, and W 79 of 32 rows
-// instead of 20 of 128 (the 2,500-node job: 71 -> 57 us); 12,788 rows 256 -> 256 in
-// bf16 have 50 tiles of 256 x 256 and 200 of 128 x 128 (two such products and the
-// loss: 88 -> 67 us).
-constexpr int64_t kFewTiles = 256;
+// Tile shapes by dtype, epilogue, output width and how many tiles there are. Where
+// the large tiles leave CUs idle, smaller ones are faster for as long as they all run
+// at once (a second round costs as much as the first, and the large tiles take the
+// same time up to one per CU). Measured, us, small / large:
+//  - row norm, 32 rows against 128 (fp32 64): up to 8,192 rows, one tile per CU. 256
+//    outputs, K = 768: bf16 14.8 / 20.0 at 8,192 rows, 20.8 / 20.2 at 10,000, 39.5 /
+//    23.4 at 26,000; fp32 40.4 / 47.8, 63.8 / 49.2; 512 outputs, K = 1,024, bf16
+//    25.6 / 40.5, 42.8 / 41.6. Up to 128 outputs, K = 384, twice the rows: bf16 10.6 /
+//    11.7 at 16,384 rows, 12.9 / 12.0 at 20,000; fp32 24.6 / 28.5, 31.0 / 29.2.
+//  - 64 x 64 against 128 x 128: bf16 K = 256, 256 outputs 10.3 / 10.6 at 200 tiles of
+//    128 x 128, 12.9 / 12.7 at 314; K = 2,048, 512 outputs 16.3 / 25.0 at 96, 26.9 / 26.1
+//    at 160, 33.6 / 26.8 at 204; fp32 K = 256, 256 outputs 18.2 / 21.6 at 128, 22.8 / 22.4
+//    at 158, 27.5 / 23.4 at 200.
+//  - bf16 128 x 128 against 256 x 256: K = 2,048, 512 outputs 40.8 / 51.2 at 100 tiles of
+//    256 x 256, 46.4 / 51.5 at 128, 62.2 / 53.3 at 158; K = 512, 256 outputs 25.8 / 25.6
+//    at 129, 25.9 / 27.2 at 176, 32.1 / 29.7 at 235; K = 256 20.1 / 20.8 at 176, 23.8 / 23.1
+//    at 235; up to 128 outputs, which leave half of a large tile empty, 15.4 / 20.4 at 235.
+inline int64_t few_norm_rows(const GemmLaunch& a) { return a.N > 128 ? 8192 : 16384; }
+inline int64_t few_tiles(const GemmLaunch& a) { return !a.bf16 || a.K0 > 512 ? 128 : 256; }
+inline int64_t mid_tiles(const GemmLaunch& a) {
+  return a.N <= 128 ? 256 : (a.K0 > 512 ? 128 : 192);
+}
 inline int64_t tiles_of(const GemmLaunch& a, int bm, int bn) {
   return ((a.M + bm - 1) / bm) * (int64_t)((a.N + bn - 1) / bn);
 }
@@ -1138,8 +1176,8 @@ template <bool BF16>
 hipError_t launch_small_norm(const GemmLaunch& a, hipStream_t s) {
   if (a.N <= 64) return launch_cfg<Cfg<BF16, 32, 64, 1, 2, true, 4>>(a, s);
   if (a.N <= 128) return launch_cfg<Cfg<BF16, 32, 128, 1, 4, true, 4>>(a, s);
-  if (a.N <= 256) return launch_cfg<Cfg<BF16, 32, 256, 1, 8, true, 3>>(a, s);
-  return launch_cfg<Cfg<BF16, 32, 512, 1, 8, true, 3>>(a, s);
+  if (a.N <= 256) return launch_cfg<Cfg<BF16, 32, 256, 1, 8, true, 3, 1, false, BF16>>(a, s);
+  return launch_cfg<Cfg<BF16, 32, 512, 1, 8, true, 3, 1, false, BF16>>(a, s);
 }
 
 template <bool PRE>
@@ -1167,18 +1205,21 @@ hipError_t launch_bf16(const GemmLaunch& a, hipStream_t s) {
 // Few tiles of the large shapes; false when there are enough.
 bool launch_few(const GemmLaunch& a, hipStream_t s, hipError_t* e) {
   if (a.l2norm) {
-    const int bm = a.bf16 || a.N <= 128 ? 128 : 64;
-    if (tiles_of(a, bm, 512) >= kFewTiles) return false;
+    if (a.M > few_norm_rows(a)) return false;
     *e = a.bf16 ? launch_small_norm<true>(a, s) : launch_small_norm<false>(a, s);
     return true;
   }
-  if (tiles_of(a, 128, 128) < kFewTiles) {
-    *e = a.bf16 ? launch_cfg<Cfg<true, 64, 64, 2, 2, false, 4>>(a, s)
-                : launch_cfg<Cfg<false, 64, 64, 2, 2, false, 4>>(a, s);
+  // In bf16, with the K order of the large kernel (gemm_rs_kernel does not rotate).
+  const bool rotate = a.bf16 && !use_rs(a);
+  if (tiles_of(a, 128, 128) < few_tiles(a)) {
+    if (!a.bf16) *e = launch_cfg<Cfg<false, 64, 64, 2, 2, false, 4>>(a, s);
+    else if (rotate) *e = launch_cfg<Cfg<true, 64, 64, 2, 2, false, 4, 1, false, true>>(a, s);
+    else *e = launch_cfg<Cfg<true, 64, 64, 2, 2, false, 4>>(a, s);
     return true;
   }
-  if (a.bf16 && tiles_of(a, 256, 256) < kFewTiles) {
-    *e = launch_cfg<Cfg<true, 128, 128, 2, 2, false, 4>>(a, s);
+  if (a.bf16 && tiles_of(a, 256, 256) < mid_tiles(a)) {
+    if (rotate) *e = launch_cfg<Cfg<true, 128, 128, 2, 2, false, 4, 1, false, true>>(a, s);
+    else *e = launch_cfg<Cfg<true, 128, 128, 2, 2, false, 4>>(a, s);
     return true;
   }
   return false;
@@ -1191,15 +1232,10 @@ size_t split_b_bytes(int N, int K) {
   return (size_t)(K / 16) * blocks * 3072 + blocks * 4;
 }
 
-hipError_t launch_gemm(GemmLaunch a, hipStream_t s) {
+hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   ProfileScope prof(a.prof_class >= 0 ? a.prof_class : (a.l2norm ? kKGemmW : (a.relu ? kKGemmQ : kKGemmR)), s);
   if (a.l2norm && a.N > 512) return hipErrorInvalidValue;
-  // The tile that the K rotation follows: the large one's, whichever runs.
-  if (a.bf16 && (a.l2norm ? a.N > 128 : !use_rs(a))) {
-    a.rot_m = a.l2norm ? 128 : 256;
-    a.rot_n = a.l2norm && a.N > 256 ? 512 : 256;
-  }
   hipError_t few = hipSuccess;
   if (launch_few(a, s, &few)) return few;
   if (use_rs(a)) return launch_rs(a, s);

@@ -195,9 +195,8 @@ struct GemmLaunch {
   // Only the K-sweep rotation reads it, so a product split into row ranges
   // sums every row in the same order as one launch over all rows.
   int64_t row_base = 0;
-  int rot_m = 0, rot_n = 0;  // tile the rotation follows, 0: none (set by the launch)
 };
-hipError_t launch_gemm(GemmLaunch a, hipStream_t s);
+hipError_t launch_gemm(const GemmLaunch& a, hipStream_t s);
 size_t split_b_bytes(int N, int K);
 
 // R[r] = ReLU(H[t(r)] Q^T + q) W_n^T for r in [0, rows), t(r) = rowmap[r] or

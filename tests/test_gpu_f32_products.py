@@ -120,8 +120,9 @@ def _check_odd(z, h, G1):
     assert not bad.any(), (int(bad.sum()), torch.nonzero(bad)[:8].tolist())
 
 
+# (Weights are split beforehand from 3 G multiply-adds on.)
 @pytest.mark.parametrize("rows,d,hidden", [(300, 64, 96), (300, 272, 16), (16500, 64, 96),
-                                           (16500, 80, 272)])
+                                           (16500, 80, 272), (70_001, 272, 176)])
 def test_operands_at_the_ends_of_the_range(rows, d, hidden):
     import paper_1806_01973_amd as ps
     print(f"[case] ends of the range {rows} x {d} -> {hidden}", flush=True)
@@ -156,12 +157,14 @@ def _norm_layer(h, x, W, self_rows, m):
                              transform_rows=tr).cpu()
 
 
-@pytest.mark.parametrize("dout", [16, 64, 128, 256, 512])
-@pytest.mark.parametrize("rows", [300, 16500])
-def test_row_norm_tiles_with_odd_rows(rows, dout):
-    """Infinities and tiny values in either source of a row-norm tile, behind a row map."""
-    print(f"[case] row-norm tiles with odd rows {rows} -> {dout}", flush=True)
-    d = m = 32
+@pytest.mark.parametrize("dout,rows,d", [(dout, rows, 32) for dout in (16, 64, 128, 256, 512)
+                                         for rows in (300, 16500)] +
+                         [(dout, (3 << 30) // (288 * dout) + 77, 144) for dout in (64, 128, 256, 512)])
+def test_row_norm_tiles_with_odd_rows(rows, dout, d):
+    """Infinities and tiny values in either source of a row-norm tile, behind a row map;
+    the last ones with the weights split beforehand."""
+    print(f"[case] row-norm tiles with odd rows {rows} x {d} -> {dout}", flush=True)
+    m = d
     g = torch.Generator().manual_seed(rows + dout)
     h, x = torch.randn((rows, d), generator=g), torch.rand((rows, m), generator=g)
     W = torch.randn((dout, d + m), generator=g) * 0.1
@@ -196,8 +199,21 @@ def test_row_norm_tiles_with_odd_rows(rows, dout):
 def test_bits_at_the_ends_of_the_range_do_not_depend_on_the_row_count():
     # Few rows split the weights in their tiles, many beforehand, in other tile shapes.
     import paper_1806_01973_amd as ps
-    h, G1 = _odd(16500, 64, 96, 5)
-    mlp = ps.DeviceMLP(G1, torch.zeros(96), torch.eye(96))
+    h, G1 = _odd(70_001, 272, 176, 5)
+    mlp = ps.DeviceMLP(G1, torch.zeros(176), torch.eye(176))
     many = _transform(mlp, h)
-    for k in (9, 70, 300):
+    for k in (9, 70, 300, 16500):
         assert torch.equal(_transform(mlp, h[:k]), many[:k]), k
+
+
+@pytest.mark.parametrize("rows,d,hidden", [(20_001, 512, 400), (70_001, 272, 176)])
+def test_products_with_weights_split_beforehand(rows, d, hidden):
+    """The fp32 bound, and the same bits from a workspace without room for the split
+    weights; both of the output layers' products split, and the first alone."""
+    import paper_1806_01973_amd as ps
+    print(f"[case] split weights {rows} x {d} -> {hidden}", flush=True)
+    mlp, h = _mlp(rows, d, hidden, rows)
+    z = ps.output_mlp(mlp, h.cuda())
+    _check(z, mlp, h)
+    small = torch.empty((rows * hidden * 4 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+    assert torch.equal(ps.output_mlp(mlp, h.cuda(), workspace=small), z)
