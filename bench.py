@@ -58,9 +58,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "node embeddings/sec (K=2 layerwise, all nodes) + walk steps/sec, 1 MI355X"
 HBM_PEAK_GBS = 8000.0
-# f32 is the fp32 MFMA rate; the kernels sum six bf16 MFMAs per fp32 product instead
-# (ceiling a sixth of the bf16 rate, 417), so their fraction of it can pass 1.
-MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
+# fp32 products are eight bf16 MFMAs each: an eighth of the bf16 rate (fp32 MFMAs: 157.3).
+MFMA_PEAK_TFLOPS = {"f32": 312.5, "bf16": 2500.0}
 PROFILE_DIR = os.path.join(ROOT, "profiles")
 DEFAULT_STEPS = {"tiny": 20, "medium": 20, "minibatch": 20, "large": 4, "shard": 5, "hardneg": 20,
                  "bipartite": 20}

@@ -48,6 +48,7 @@
 // 512: 2.34 ms (112 TFLOP/s) with fp32 MFMAs, 1.93 (136) so; 512 -> 256: 2.20,
 // 1.75; 1.2M rows of the W layer (768 -> 256, norm): 4.12, 3.09 (153 TFLOP/s). Looking
 // for the least magnitudes is 1-6% of that.
+// (The row-norm tiles of 256 and 512 columns keep up to 56 bytes a lane in scratch.)
 // (The remainders as two-element bf16 dot products are fewer instructions, but
 // those run on the matrix pipe: 9% slower.)
 //

@@ -55,7 +55,8 @@ __global__ void permute_ws_kernel(const uint16_t* __restrict__ W, int64_t ldw,
 }
 
 // FULL: 32 rows per wave and turn (a.group otherwise; as a variable it costs the
-// loop registers).
+// loop registers, 124 bytes of scratch a lane against 20, and the launches that take
+// it are still faster so: see launch_pool_w).
 template <int MODE, bool FULL>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void pool_w_kernel(PoolWLaunch a) {

@@ -54,7 +54,7 @@ def test_algorithmic_work_per_launch():
     assert k["gemm_r"]["algo_flops_per_launch"] == pytest.approx(2.0 * P * 512 * 256)
     assert k["gemm_w"]["algo_flops_per_launch"] == pytest.approx(2.0 * N * 256 * 256)
     assert k["gemm_w"]["frac_mfma"] == pytest.approx(
-        2.0 * N * 256 * 256 / 1.5e-3 / 1e12 / 157.3)
+        2.0 * N * 256 * 256 / 1.5e-3 / 1e12 / 312.5)
     # Walk: 12 B per edge step with int32 row offsets.
     assert k["walk_topt"]["algo_bytes_per_launch"] == pytest.approx(steps * 12)
     # Pool then dense: the pool gathers m-wide rows and W has K = d_in + m.
@@ -86,7 +86,7 @@ def test_dominant_kernel_roofline_and_traffic(monkeypatch, tmp_path):
     # A GEMM-dominated step reports the MFMA roofline for its dtype and no traffic.
     k["gemm_q"]["ms_per_step"] = 100.0
     r = bench.roofline_of(k, wl)
-    assert r["kernel"] == "gemm_q" and r["bound"] == "mfma" and r["peak"] == 157.3
+    assert r["kernel"] == "gemm_q" and r["bound"] == "mfma" and r["peak"] == 312.5
     assert r["traffic"] is None
 
 
