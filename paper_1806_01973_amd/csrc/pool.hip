@@ -428,7 +428,7 @@ __global__ __launch_bounds__(1024) void pool_probe_kernel(PoolLaunch a, int min_
 // are added by halving (each step exchanges half of the values a lane still
 // holds), in the same tree as a butterfly. pool_probe_kernel decides; this kernel
 // and pool_kernel (whole rows, launched behind it) each end at once if not chosen
-// (with the probe 10 to 30 us where whole rows are).
+// (with the probe about 35 us where whole rows are).
 // What bounds it: cache bandwidth, about 13 TB/s of gathered bytes, and at 128
 // bytes an item the issue slots. T = 50, pin degree Zipf(2): 1M rows of 1 KB
 // (fp32) 6.60 -> 5.19 ms; 300K of 1 KB (bf16) 1.72 -> 1.36; 100K of 2 KB, max
@@ -668,7 +668,7 @@ hipError_t launch_typed(const PoolLaunch& a, hipStream_t s) {
 
 // Pools the slabs are for: tables of rows of 1 KB and more, 48 MB and more (byte
 // offsets are 32 bits), and 8 GB or more to gather (about 1.2 ms), beside which the
-// probe and the empty launch, 10 to 20 us, count little.
+// probe and the empty launch, about 35 us, count little.
 bool pool_slabs_wanted(int64_t n_transform, int64_t row_bytes, int64_t rows, int T) {
   const int64_t table = n_transform * row_bytes;
   return row_bytes >= 1024 && table >= (48ll << 20) && table < (1ll << 32) - 16 &&
