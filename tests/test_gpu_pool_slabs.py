@@ -121,3 +121,24 @@ def test_the_choice_does_not_depend_on_the_workspace():
     assert small.numel() < ps.convolve_workspace_size(layer, n, rows)
     self_rows = torch.zeros(rows, dtype=torch.int32, device="cuda")
     assert torch.equal(ps.convolve_layer(layer, h, n, nbr, self_rows=self_rows, workspace=small), out)
+
+
+def test_output_over_the_self_rows():
+    """A layer that writes its rows over the self rows it reads: the choice must not lie
+    there, so the pool takes whole rows (the bits of a call of few rows)."""
+    import paper_1806_01973_amd as ps
+    n, m, T, rows = 60_000, 256, 64, 140_001
+    layer, _, nbr, _ = _run(torch.float32, n, m, T, rows, "importance", True, False, True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    W = torch.randn((m, 2 * m), generator=g, device="cuda") * 0.05
+    layer = ps.DeviceLayer(torch.eye(m, device="cuda"), torch.zeros(m), W, torch.zeros(m))
+    h = torch.rand((rows, m), generator=g, device="cuda")
+    k = 5_000
+    part = ps.Neighborhoods(nbr.idx[:k], nbr.counts[:k], nbr.weights[:k])
+    want = ps.convolve_layer(layer, h, n, part)
+    apart = ps.convolve_layer(layer, h, n, nbr)
+    assert not torch.equal(apart[:k], want)  # slabs
+    ps.convolve_layer(layer, h, n, nbr, out=h)
+    assert torch.equal(h[:k], want)
+    # Entries of unit rows: another order of T weighted values moves them by under 2 T 2^-24.
+    assert (h - apart).abs().max() <= 2 * T * 2.0 ** -24
